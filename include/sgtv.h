@@ -334,9 +334,11 @@ int sgtv_backprojection_noalloc(sgtv_ctx ctx, float *x, int mem_kind);
  *     straight from memory (no other field applies).
  *   variant: inner loop of the tiled products: 1 one batch of entries in
  *     flight per wave, 2 two batches, 3 two batches plus the next column block
- *     read ahead into registers (0: automatic).  Variant 1 stores the
- *     entries' indices in 24 bits (three bytes per entry instead of four)
- *     when 64 <= rows_per_wave <= 1024 and block_cols <= 16380, or
+ *     read ahead into registers (0: automatic).  Variant 1 streams its lists
+ *     with two-byte indices where rows_per_wave >= 64, block_cols <= 16380 is a
+ *     multiple of 4 and at most 1024 * waves, and the matrix is dense enough for
+ *     it; else it stores the indices in 24 bits (three bytes per entry instead
+ *     of four) when 64 <= rows_per_wave <= 1024 and block_cols <= 16380, or
  *     1024 < rows_per_wave <= 2048 and block_cols <= 8188.
  * Limits: waves in [1, 16]; rows_per_wave in [1, 32767]; block_cols a
  * multiple of 4 in [4, 65536]; slabs in [1, 16]; the LDS of one workgroup,

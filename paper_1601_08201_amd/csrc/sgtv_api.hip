@@ -376,34 +376,57 @@ void transpose_csr(int64_t I, int64_t J, const std::vector<int64_t> &rp, const s
     });
 }
 
-// Host packing of one tiled product from CSR-like lines (rows of M in order,
-// column indices ascending within a row).  V is float or a 16-bit code.
-template <class V>
-int build_tiled(int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp,
-                const std::vector<int32_t> &ci, const std::vector<V> &vals, const TileParams &t,
-                bool idx24, std::vector<int32_t> &pk, std::vector<V> &pv, std::vector<int32_t> &goff,
-                std::vector<int32_t> &poff, std::vector<uint16_t> &slot_of, sgtv::TileMap &map) {
-    // 24-bit indices: row in 10 bits and column in 14 (up to 1024 rows per
-    // wave), or 11 and 13 (up to 2048), with the code cb left for the zero
-    // slot.  Their lists are lane-owned: all entries of a row within a list sit
-    // in one lane, in row order, so a lane can read every accumulator of a
-    // window of entries at once (no other lane touches its rows)
-    idx24 = idx24 && sgtv::idx24_fits(t.rw, t.cb);
-    const int row_shift = idx24 ? sgtv::idx24_col_bits(t.rw) : 16;
+// The lists of a tiled copy: which rows every wave owns in every tile and,
+// for lane-owned formats, the entries of every list (row block, slab, column
+// block, wave) in the order of the wave's rows.
+struct TileLists {
+    TileParams t{};
+    int64_t n_rows = 0, n_cols = 0, RB = 0, n_rb = 0, n_lists = 0;
+    int cbs_max = 0;
+    bool balance = false;              // rows are dealt to the waves (slot_of)
+    std::vector<int> slab_begin, slab_of;
+    std::vector<uint16_t> slot_of;
+    std::vector<int32_t> count, maxrun;
+    std::vector<int64_t> lstart, lent;   // first entry of every list; entries (indices into ci / vals)
+    std::vector<int16_t> lrow;           // row within the wave of every listed entry
+
+    // slot (wave * rw + row in the wave) of row r in the tile of column c
+    int64_t slot_in_tile(int64_t r, int32_t c) const {
+        const int64_t rb = r / RB, i = r - rb * RB;
+        if (!balance) return i;
+        const int slab = slab_of[c / t.cb];
+        return slot_of[static_cast<size_t>((rb * t.ns + slab) * RB + i)];
+    }
+    int64_t list_of(int64_t r, int32_t c) const {
+        const int64_t rb = r / RB;
+        const int64_t w = slot_in_tile(r, c) / t.rw;
+        const int64_t cbi = c / t.cb;
+        const int slab = slab_of[cbi];
+        return ((rb * t.ns + slab) * cbs_max + (cbi - slab_begin[slab])) * t.waves + w;
+    }
+};
+
+// entries: also fill lstart, lent and lrow (lane-owned formats).
+void plan_lists(int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp, const std::vector<int32_t> &ci,
+                const TileParams &t, bool entries, TileLists &P) {
     SetupClock clk;
     const int64_t RB = static_cast<int64_t>(t.waves) * t.rw;
     const int64_t n_rb = (n_rows + RB - 1) / RB;
     const int64_t ncb = (n_cols + t.cb - 1) / t.cb;
     const int ns = t.ns;
-    std::vector<int> slab_begin(ns + 1);
+    std::vector<int> &slab_begin = P.slab_begin, &slab_of = P.slab_of;
+    slab_begin.resize(ns + 1);
     for (int k = 0; k <= ns; ++k) slab_begin[k] = static_cast<int>((k * ncb) / ns);
     int cbs_max = 0;
     for (int k = 0; k < ns; ++k) cbs_max = std::max(cbs_max, slab_begin[k + 1] - slab_begin[k]);
-    std::vector<int> slab_of(static_cast<size_t>(ncb));
+    slab_of.resize(static_cast<size_t>(ncb));
     for (int k = 0; k < ns; ++k)
         for (int b = slab_begin[k]; b < slab_begin[k + 1]; ++b) slab_of[b] = k;
     const int64_t n_lists = n_rb * ns * cbs_max * t.waves;
-    // 24-bit lists: in every tile (row block, slab) the rows of the row block
+    P.t = t;
+    P.n_rows = n_rows; P.n_cols = n_cols; P.RB = RB; P.n_rb = n_rb; P.n_lists = n_lists;
+    P.cbs_max = cbs_max;
+    // Lane-owned lists: in every tile (row block, slab) the rows of the row block
     // are dealt to the waves so that each wave's share of every column block is
     // as even as possible (every block ends at a barrier, where all waves wait
     // for the longest list).  Greedy: rows by decreasing entry count, each to
@@ -413,8 +436,9 @@ int build_tiled(int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp,
     // order through it).  The 32-bit lists, and schedules whose per-row-block
     // counts would pass 2^24 (tiny column blocks of a large matrix), keep row
     // offset i in slot i.
+    std::vector<uint16_t> &slot_of = P.slot_of;
     slot_of.clear();
-    const bool balance = idx24 && static_cast<int64_t>(ns) * RB * cbs_max <= (int64_t(1) << 24);
+    const bool balance = entries && static_cast<int64_t>(ns) * RB * cbs_max <= (int64_t(1) << 24);
     if (balance) {
         slot_of.assign(static_cast<size_t>(n_rb * ns * RB), 0);
         // row blocks are independent: each worker takes every nth one
@@ -477,34 +501,31 @@ int build_tiled(int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp,
                         for (size_t u = 0; u < nzc.size(); ++u) lw[nzc[u]] += nzn[u];
                         wtot[best] += tot[i];
                     }
+                    // within a wave the slots follow the order of its rows, so that
+                    // lists filled row by row are in slot order
+                    std::fill(filled.begin(), filled.end(), 0);
+                    for (int64_t i = 0; i < RB; ++i) {
+                        uint16_t &sl = slot_of[static_cast<size_t>(tile * RB + i)];
+                        const int w = sl / t.rw;
+                        sl = static_cast<uint16_t>(w * t.rw + filled[w]++);
+                    }
                 }
             }
         });
     }
+    P.balance = balance;
     clk.mark("  rows dealt to waves");
-    // slot (wave * rw + row in the wave) of row r in the tile of column c
-    auto slot_in_tile = [&](int64_t r, int32_t c) -> int64_t {
-        const int64_t rb = r / RB, i = r - rb * RB;
-        if (!balance) return i;
-        const int slab = slab_of[c / t.cb];
-        return slot_of[static_cast<size_t>((rb * ns + slab) * RB + i)];
-    };
-    auto list_of = [&](int64_t r, int32_t c) -> int64_t {
-        const int64_t rb = r / RB;
-        const int64_t w = slot_in_tile(r, c) / t.rw;
-        const int64_t cbi = c / t.cb;
-        const int slab = slab_of[cbi];
-        return ((rb * ns + slab) * cbs_max + (cbi - slab_begin[slab])) * t.waves + w;
-    };
-    std::vector<int32_t> count(static_cast<size_t>(n_lists), 0), run(static_cast<size_t>(n_lists), 0),
-        maxrun(static_cast<size_t>(n_lists), 0);
+    std::vector<int32_t> &count = P.count, &maxrun = P.maxrun;
+    count.assign(static_cast<size_t>(n_lists), 0);
+    maxrun.assign(static_cast<size_t>(n_lists), 0);
+    std::vector<int32_t> run(static_cast<size_t>(n_lists), 0);
     std::vector<int64_t> last(static_cast<size_t>(n_lists), -1);
     // the lists of a row block hold only its rows: workers take whole row blocks
     on_threads(n_rb, [&](int64_t first, int64_t step) {
         for (int64_t rb = first; rb < n_rb; rb += step)
             for (int64_t r = rb * RB; r < std::min(n_rows, (rb + 1) * RB); ++r)
                 for (int64_t k = rp[r]; k < rp[r + 1]; ++k) {
-                    const int64_t L = list_of(r, ci[k]);
+                    const int64_t L = P.list_of(r, ci[k]);
                     count[L]++;
                     run[L] = last[L] == r ? run[L] + 1 : 1;
                     last[L] = r;
@@ -512,10 +533,9 @@ int build_tiled(int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp,
                 }
     });
     clk.mark("  list counts");
-    // idx24: the entries (indices into ci / vals) of every list, in row order
-    std::vector<int64_t> lstart, lent;
-    std::vector<int16_t> lrow;   // row within the wave of every listed entry
-    if (idx24) {
+    if (entries) {
+        std::vector<int64_t> &lstart = P.lstart, &lent = P.lent;
+        std::vector<int16_t> &lrow = P.lrow;
         lstart.assign(static_cast<size_t>(n_lists + 1), 0);
         for (int64_t L = 0; L < n_lists; ++L) lstart[L + 1] = lstart[L] + count[L];
         lent.resize(static_cast<size_t>(lstart[n_lists]));
@@ -525,13 +545,33 @@ int build_tiled(int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp,
             for (int64_t rb = first; rb < n_rb; rb += step)
                 for (int64_t r = rb * RB; r < std::min(n_rows, (rb + 1) * RB); ++r)
                     for (int64_t k = rp[r]; k < rp[r + 1]; ++k) {
-                        const int64_t at = cur[list_of(r, ci[k])]++;
+                        const int64_t at = cur[P.list_of(r, ci[k])]++;
                         lent[at] = k;
-                        lrow[at] = static_cast<int16_t>(slot_in_tile(r, ci[k]) % t.rw);
+                        lrow[at] = static_cast<int16_t>(P.slot_in_tile(r, ci[k]) % t.rw);
                     }
         });
     }
     clk.mark("  list filling");
+}
+
+// Host packing of one tiled product from CSR-like lines (rows of M in order,
+// column indices ascending within a row).  V is float or a 16-bit code.
+// The lists in groups of 64 entries with 24-bit or 32-bit indices.
+template <class V>
+int place_lists(TileLists &P, const std::vector<int64_t> &rp, const std::vector<int32_t> &ci,
+                const std::vector<V> &vals, bool idx24, std::vector<int32_t> &pk, std::vector<V> &pv,
+                std::vector<int32_t> &goff, std::vector<int32_t> &poff, sgtv::TileMap &map) {
+    SetupClock clk;
+    const TileParams &t = P.t;
+    const int ns = t.ns, cbs_max = P.cbs_max;
+    const int64_t n_rows = P.n_rows, n_cols = P.n_cols, RB = P.RB, n_rb = P.n_rb, n_lists = P.n_lists;
+    const std::vector<int> &slab_begin = P.slab_begin;
+    std::vector<int32_t> &count = P.count;
+    const std::vector<int32_t> &maxrun = P.maxrun;
+    const std::vector<int64_t> &lstart = P.lstart, &lent = P.lent;
+    const std::vector<int16_t> &lrow = P.lrow;
+    const int row_shift = idx24 ? sgtv::idx24_col_bits(t.rw) : 16;
+    auto list_of = [&](int64_t r, int32_t c) { return P.list_of(r, c); };
     // Lane-owned layout of list L: runs of equal rows, longest first (ties in
     // row order), each to the least-loaded lane (ties: lowest lane); a lane
     // keeps its runs in row order.  Fills lane_load[64] and, in lane order,
@@ -766,6 +806,180 @@ int build_tiled(int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp,
     return SGTV_OK;
 }
 
+// The lists as streams of 16-bit indices (TileMap::idx24 == kIdxStream, see
+// sgtv_tiled.hip).  A list's runs of equal rows, in row order, are dealt to the
+// lanes in order: a lane takes runs until it holds T entries, with T the least
+// that 64 lanes can do with; a step of more than dmax rows inside a lane costs
+// padding entries of dmax rows each.  Leaves the outputs empty and returns
+// SGTV_OK when the format does not pay:
+//   * fewer than kStreamBlocks column blocks a slab: there are no barriers to
+//     stream across, and 24-bit lists, whose lanes take rows in any order, pack
+//     tighter (64^3 scanner, 2 blocks: 53.6 against 51.2 us an iteration; 16
+//     scans of 9 x 41 x 54, 1 and 2 blocks: 57.4 against 56.2 us);
+//   * more than 1.35 times the groups that dense lists would have.
+constexpr int kStreamBlocks = 3;
+template <class V>
+int stream_lists(const TileLists &P, const std::vector<int32_t> &ci, const std::vector<V> &vals,
+                 std::vector<int32_t> &pk, std::vector<V> &pv, std::vector<int32_t> &goff,
+                 std::vector<int32_t> &poff, sgtv::TileMap &map) {
+    SetupClock clk;
+    constexpr int kC = sgtv::kStreamChunk;
+    const TileParams &t = P.t;
+    const int cbits = sgtv::stream_col_bits(t.cb, t.waves), dmax = (1 << (16 - cbits)) - 1;
+    const int64_t n_streams = P.n_rb * t.ns * t.waves;
+    if (P.cbs_max < kStreamBlocks) return SGTV_OK;
+    for (int k = 0; k < t.ns; ++k)   // the kernel takes a slab to have a block
+        if (P.slab_begin[k] == P.slab_begin[k + 1]) return SGTV_OK;
+    struct Run {
+        int32_t row, len;
+    };
+    // lanes that lists of runs need with at most T entries per lane; emit(run,
+    // lane, position of its first entry, padding entries before it)
+    auto deal = [&](const std::vector<Run> &runs, int64_t T, auto &&emit) -> int64_t {
+        int64_t lane = -1, load = T, at = 0;
+        for (size_t q = 0; q < runs.size(); ++q) {
+            const int64_t gap = runs[q].row - at;
+            const int64_t pads = gap > dmax ? (gap - 1) / dmax : 0;
+            if (lane < 0 || load + pads + runs[q].len > T) {
+                ++lane;
+                emit(q, lane, int64_t(0), int64_t(0));
+                load = runs[q].len;
+            } else {
+                emit(q, lane, load, pads);
+                load += pads + runs[q].len;
+            }
+            at = runs[q].row;
+        }
+        return lane + 1;
+    };
+    auto runs_of = [&](int64_t L, std::vector<Run> &runs) -> int64_t {
+        runs.clear();
+        int32_t longest = 0;
+        for (int64_t i = P.lstart[L]; i < P.lstart[L + 1]; ++i) {
+            if (runs.empty() || runs.back().row != P.lrow[i]) runs.push_back({P.lrow[i], 0});
+            longest = std::max(longest, ++runs.back().len);
+        }
+        return longest;
+    };
+    // groups of every list; streams (tile, wave) are independent
+    std::vector<int32_t> ngr(static_cast<size_t>(P.n_lists), 0);
+    std::vector<int64_t> groups(static_cast<size_t>(n_streams), 0);
+    auto list_at = [&](int64_t s, int64_t c) { return (s / t.waves * P.cbs_max + c) * t.waves + s % t.waves; };
+    on_threads(n_streams, [&](int64_t first, int64_t step) {
+        std::vector<Run> runs;
+        for (int64_t s = first; s < n_streams; s += step)
+            for (int64_t c = 0; c < P.cbs_max; ++c) {
+                const int64_t L = list_at(s, c), n = P.lstart[L + 1] - P.lstart[L];
+                if (n == 0) continue;
+                int64_t T = std::max(runs_of(L, runs), (n + 63) / 64);
+                for (;;) {
+                    const int64_t k = deal(runs, T, [](size_t, int64_t, int64_t, int64_t) {});
+                    if (k <= 64) break;
+                    T += std::max<int64_t>(1, (k - 64) * T / 128);
+                }
+                ngr[L] = static_cast<int32_t>(std::min<int64_t>(T, int64_t(1) << 24));
+                groups[s] += T;
+            }
+    });
+    clk.mark("  stream sizes");
+    int64_t total = 0, dense = 0, stored = 0;
+    for (int64_t s = 0; s < n_streams; ++s) {
+        total += (groups[s] + kC - 1) / kC;
+        stored += groups[s];
+        if (groups[s] >= (int64_t(1) << 30)) return SGTV_OK;
+    }
+    for (int64_t L = 0; L < P.n_lists; ++L)
+        dense += std::max<int64_t>((P.count[L] + 63) / 64, P.maxrun[L]);
+    if (total * kC * 64 >= (int64_t(1) << 31) || stored * 20 > dense * 27) return SGTV_OK;
+    goff.assign(static_cast<size_t>(P.n_lists + 1), 0);
+    poff.assign(static_cast<size_t>(n_streams + 1 + P.n_lists * 32), 0);
+    pk.assign(static_cast<size_t>((total + 1) * 256), static_cast<int32_t>(t.cb | (t.cb << 16)));
+    pv.assign(static_cast<size_t>((total + 1) * kC * 64), V(0));
+    total = 0;
+    for (int64_t s = 0; s < n_streams; ++s) {
+        poff[s] = static_cast<int32_t>(total);
+        total += (groups[s] + kC - 1) / kC;
+    }
+    poff[n_streams] = static_cast<int32_t>(total);
+    uint16_t *idx = reinterpret_cast<uint16_t *>(pk.data());
+    uint16_t *bases = reinterpret_cast<uint16_t *>(poff.data() + n_streams + 1);
+    const int acc_floats = (t.waves * t.rw + 3) / 4 * 4;
+    on_threads(n_streams, [&](int64_t first, int64_t step) {
+        std::vector<Run> runs;
+        for (int64_t s = first; s < n_streams; s += step) {
+            int64_t end = 0;
+            const int w = static_cast<int>(s % t.waves);
+            for (int64_t c = 0; c < P.cbs_max; ++c) {
+                const int64_t L = list_at(s, c), g0 = end;
+                end += ngr[L];
+                goff[L] = static_cast<int32_t>(end);
+                // lanes without entries stay on the spare zero beside the zero slot
+                uint16_t *base = bases + L * 64;
+                std::fill(base, base + 64, static_cast<uint16_t>(acc_floats + t.cb + 1 - w * t.rw));
+                if (P.lstart[L] == P.lstart[L + 1]) continue;
+                runs_of(L, runs);
+                int64_t k = P.lstart[L];
+                int32_t at = 0;
+                auto put = [&](int64_t lane, int64_t i, int code, V v) {
+                    const int64_t g = g0 + i, ch = poff[s] + g / kC, e = g % kC;
+                    idx[(ch * 64 + lane) * kC + e] = static_cast<uint16_t>(code);
+                    if (sizeof(V) == 4) pv[((ch * 2 + e / 4) * 64 + lane) * 4 + e % 4] = v;
+                    else pv[(ch * 64 + lane) * kC + e] = v;
+                };
+                deal(runs, ngr[L], [&](size_t q, int64_t lane, int64_t i, int64_t pads) {
+                    if (i == 0) {
+                        base[lane] = static_cast<uint16_t>(runs[q].row);
+                        at = runs[q].row;
+                    }
+                    for (int64_t u = 0; u < pads; ++u) {
+                        put(lane, i++, (dmax << cbits) | t.cb, V(0));
+                        at += dmax;
+                    }
+                    for (int32_t u = 0; u < runs[q].len; ++u, ++k) {
+                        const int64_t e = P.lent[k];
+                        put(lane, i++, ((runs[q].row - at) << cbits) | (ci[e] % t.cb), vals[e]);
+                        at = runs[q].row;
+                    }
+                });
+            }
+        }
+    });
+    clk.mark("  stream placement");
+    map = sgtv::TileMap{};
+    map.idx24 = sgtv::kIdxStream;
+    map.n_rows = P.n_rows;
+    map.n_cols = P.n_cols;
+    map.n_rb = P.n_rb;
+    map.pad = n_streams + 1;
+    map.rw = t.rw;
+    map.waves = t.waves;
+    map.cb = t.cb;
+    map.ns = t.ns;
+    map.cbs_max = P.cbs_max;
+    map.variant = 0;
+    map.cbits = cbits;
+    for (int k = 0; k <= t.ns; ++k) map.slab_begin[k] = P.slab_begin[k];
+    return SGTV_OK;
+}
+
+template <class V>
+int build_tiled(int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp,
+                const std::vector<int32_t> &ci, const std::vector<V> &vals, const TileParams &t,
+                bool idx24, std::vector<int32_t> &pk, std::vector<V> &pv, std::vector<int32_t> &goff,
+                std::vector<int32_t> &poff, std::vector<uint16_t> &slot_of, sgtv::TileMap &map) {
+    // 24-bit indices: row in 10 bits and column in 14 (up to 1024 rows per
+    // wave), or 11 and 13 (up to 2048), with the code cb left for the zero
+    // slot.  Their lists are lane-owned: all entries of a row within a list sit
+    // in one lane, in row order, so a lane can read every accumulator of a
+    // window of entries at once (no other lane touches its rows)
+    idx24 = idx24 && sgtv::idx24_fits(t.rw, t.cb);
+    TileLists P;
+    plan_lists(n_rows, n_cols, rp, ci, t, idx24, P);
+    const int e = place_lists(P, rp, ci, vals, idx24, pk, pv, goff, poff, map);
+    slot_of.swap(P.slot_of);
+    return e;
+}
+
 // Host image of one tiled copy (what the device buffers will hold).
 struct PackedTiled {
     std::vector<int32_t> pk, goff, poff;
@@ -779,8 +993,18 @@ template <class V>
 int pack_tiled(PackedTiled &T, int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp,
                const std::vector<int32_t> &ci, const std::vector<V> &vals, const TileParams &t, bool idx24) {
     std::vector<V> pv;
-    if (int e = build_tiled(n_rows, n_cols, rp, ci, vals, t, idx24, T.pk, pv, T.goff, T.poff, T.slot, T.map))
-        return e;
+    // the simple loop reads streamed lists where the tile fits them and the
+    // matrix is dense enough, else 24-bit or 32-bit indices
+    const bool stream = idx24 && sgtv::stream_fits(t.rw, t.cb, t.waves) &&
+                        sgtv::tiled_lds_bytes(t.waves, t.rw, t.cb, true) <= 163840;
+    idx24 = idx24 && sgtv::idx24_fits(t.rw, t.cb);
+    TileLists P;
+    plan_lists(n_rows, n_cols, rp, ci, t, stream || idx24, P);
+    if (stream)
+        if (int e = stream_lists(P, ci, vals, T.pk, pv, T.goff, T.poff, T.map)) return e;
+    if (T.pk.empty())
+        if (int e = place_lists(P, rp, ci, vals, idx24, T.pk, pv, T.goff, T.poff, T.map)) return e;
+    T.slot.swap(P.slot_of);
     if constexpr (sizeof(V) == 4) T.v32.swap(pv);
     else T.v16.swap(pv);
     return SGTV_OK;
@@ -1706,7 +1930,8 @@ namespace {
 // per host thread, and every chunk is hashed on the way; an array's hash
 // folds its chunk hashes in order, so it does not depend on the threads.
 constexpr char kSysMagic[8] = {'S', 'G', 'T', 'V', 'S', 'Y', 'S', '1'};
-constexpr uint32_t kSysVersion = 3;
+constexpr uint32_t kSysVersion = 4;
+constexpr uint32_t kSysVersionUnstreamed = 3;   // the same layout, written before there were streamed lists
 constexpr size_t kIoChunk = size_t(8) << 20;
 constexpr int kSysArrays = 20;
 
@@ -1953,7 +2178,8 @@ int sgtv_load_system(sgtv_ctx ctx, const char *path) {
         const std::string bad = std::string(path) + " is not a system file of this library version";
         FileHead fh{};
         if (::pread(fc.fd, &fh, sizeof(fh), 0) != static_cast<ssize_t>(sizeof(fh)) ||
-            std::memcmp(fh.magic, kSysMagic, 8) != 0 || fh.version != kSysVersion ||
+            std::memcmp(fh.magic, kSysMagic, 8) != 0 ||
+            (fh.version != kSysVersion && fh.version != kSysVersionUnstreamed) ||
             fh.meta_bytes != sizeof(SysMeta) || fh.map_bytes != sizeof(sgtv::TileMap) ||
             fh.n_arrays != kSysArrays || fh.n_perm < 0 || fh.n_perm > (int64_t(1) << 31))
             return fail(SGTV_EINVAL, bad);
@@ -2013,7 +2239,9 @@ int sgtv_load_system(sgtv_ctx ctx, const char *path) {
                 const sgtv::TileMap &t = T->map;
                 const int64_t n_lists = t.n_rb * static_cast<int64_t>(t.ns) * t.cbs_max * t.waves;
                 sizes_ok = sizes_ok && t.ns >= 1 && t.ns <= sgtv::kMaxSlabs && n_lists >= 0 &&
-                           rec_of(T->goff).bytes == 4 * (n_lists + 1);
+                           rec_of(T->goff).bytes == 4 * (n_lists + 1) &&
+                           (t.idx24 != sgtv::kIdxStream ||
+                            rec_of(T->poff).bytes == 4 * (t.n_rb * t.ns * t.waves + 1 + 32 * n_lists));
             }
         if (!sizes_ok) return fail(SGTV_EINVAL, std::string(path) + ": inconsistent arrays");
         for (size_t a = 0; a < bufs.size(); ++a)
@@ -2471,10 +2699,11 @@ int64_t sgtv_workspace_bytes(int64_t I, int64_t J, int64_t nnz, int storage_dtyp
         const double e = static_cast<double>(nnz) / lists;
         const double groups = std::max(std::ceil(e / 64.0) + 1.0, std::ceil(lam + 2.5 * std::sqrt(lam) + 1.0));
         const double stored = std::min(lists * 64.0 * groups, 64.0 * static_cast<double>(nnz) + 256.0);
-        const bool i24 = sgtv::idx24_fits(t.rw, t.cb);
-        const double idx_bytes = i24 ? 3.0 : 4.0;
-        // 24-bit lists also keep the row order of every tile (2 bytes per row and slab)
-        const double order = i24 ? 2.0 * n_rb * 16.0 * t.rw * t.ns : 0.0;
+        // the automatic schedule streams its lists: two-byte indices and 64
+        // two-byte base rows a list, and the row order of every tile (2 bytes
+        // per row and slab)
+        const double idx_bytes = 2.0;
+        const double order = lists * 128.0 + 2.0 * n_rb * 16.0 * t.rw * t.ns;
         return stored * (idx_bytes + vb) + lists * 8.0 + order;
     };
     int64_t ns_f = 1, ns_b = 1;
@@ -2668,6 +2897,7 @@ struct sgtv_batch_s {
     DBuf rblocks, vblocks, sblocks;
     int64_t n_tiles_f = 0, n_tiles_b = 0, n_rblocks = 0, n_vblocks = 0, n_sblocks = 0;
     size_t lds_f = 0, lds_b = 0;
+    bool streamed = false;       // some scan has streamed lists
     int waves = 16, variant = 1;
     int storage = SGTV_F32;           // value type of every scan's matrix (one product launch per type)
     int fcur = 0, vcur = 0;
@@ -2710,11 +2940,13 @@ int batch_tables(sgtv_batch_s *b) {
     std::vector<sgtv::ScanDev> sd(n);
     std::vector<sgtv::BatchBlock> rbl, vbl, sbl;
     b->lds_f = b->lds_b = 0;
+    b->streamed = false;
     for (size_t i = 0; i < n; ++i) {
         sgtv_ctx_s *c = b->scans[i];
         const System &S = *c->sys;
         mf[i] = S.fwd.map;
         mb[i] = S.back.map;
+        if (mf[i].idx24 == sgtv::kIdxStream || mb[i].idx24 == sgtv::kIdxStream) b->streamed = true;
         // the forward product reads the image, or its scaled copy for 16-bit values
         xf0[i] = S.vt == SGTV_F32 ? c->f[0].as<float>() : c->fs.as<float>();
         xf1[i] = S.vt == SGTV_F32 ? c->f[1].as<float>() : c->fs.as<float>();
@@ -2870,10 +3102,10 @@ int batch_persistent(sgtv_batch_s *b, int n_iters) {
         const size_t lds = std::max(b->lds_f, b->lds_b);
         const int threads = b->waves * sgtv::kWave;
         const char *what = "";
-        if (hipError_t e = sgtv::persistent_grid(b->variant, threads, lds, &b->persistent_grid, &what))
+        if (hipError_t e = sgtv::persistent_grid(b->variant, b->streamed, threads, lds, &b->persistent_grid, &what))
             return hip_fail(e, (std::string("persistent launch: ") + what).c_str());
         if (hipError_t e = sgtv::launch_admm_persistent(b->pdev.as<sgtv::PersistentDev>(), plan, lds, threads,
-                                                        b->variant, b->persistent_grid, b->stream))
+                                                        b->variant, b->streamed, b->persistent_grid, b->stream))
             return hip_fail(e, ("persistent launch: hipLaunchCooperativeKernel (grid " +
                                 std::to_string(b->persistent_grid) + " x " + std::to_string(threads) +
                                 " threads, " + std::to_string(lds) + " bytes of LDS)").c_str());

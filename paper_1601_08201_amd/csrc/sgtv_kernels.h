@@ -55,6 +55,15 @@ inline int idx24_col_bits(int rw) { return rw <= 1024 ? 14 : 13; }
 inline bool idx24_fits(int rw, int cb) {
     return rw >= 64 && rw <= 2048 && cb % 4 == 0 && cb <= (1 << idx24_col_bits(rw)) - 4;
 }
+// The streamed format: 16-bit indices delta << c | column, c = 13 column bits
+// for blocks of up to 8188 columns that one read of two float4 per thread
+// covers, else 14 (four float4, up to 16380 columns).
+constexpr int kIdxStream = 2;      // TileMap::idx24 of a streamed copy
+constexpr int kStreamChunk = 8;    // groups per chunk
+inline int stream_col_bits(int cb, int waves) { return cb <= 8188 && cb <= 8 * waves * kWave ? 13 : 14; }
+inline bool stream_fits(int rw, int cb, int waves) {
+    return rw >= 64 && cb % 4 == 0 && cb <= 16380 && cb <= 16 * waves * kWave;
+}
 // LDS of one tiled workgroup: the row sums (a spare padding row per wave with
 // 32-bit indices), then the column block (and the zero slot with 24-bit ones)
 inline size_t tiled_lds_bytes(int waves, int rw, int cb, bool idx24) {
@@ -66,18 +75,22 @@ inline size_t tiled_lds_bytes(int waves, int rw, int cb, bool idx24) {
 struct TileMap {
     const int32_t *pk;      // packed (row in wave, column in block), padding: row = rw
     const void *val;        // values or 16-bit codes, padding: 0
-    const int32_t *goff;    // group offset of every list, n_lists + 1 entries
-    const int32_t *poff;    // 24-bit indices: offset (in dwords) of every list's indices
+    const int32_t *goff;    // group offset of every list, n_lists + 1 entries; streamed: the
+                            // group of the wave's stream at which every list ends
+    const int32_t *poff;    // 24-bit indices: offset (in dwords) of every list's indices;
+                            // streamed: first chunk of every (tile, wave) and the end, then from
+                            // dword `pad` on the 64 base rows of every list (uint16)
     const uint16_t *slot;   // 24-bit indices: per tile, the slot w * rw + l (wave w, row l
                             // in the wave) of every row of the row block; nullptr: identity
     int idx24;              // 1: indices row << cbits | column, three dwords per lane and batch;
-                            // padding: a row unused in its group, column cb (a zero in LDS)
+                            // padding: a row unused in its group, column cb (a zero in LDS);
+                            // kIdxStream: streamed lists (see sgtv_tiled.hip)
     int64_t n_rows, n_cols;
     int64_t n_rb;           // row blocks
     int64_t pad;            // entry offset of one all-padding batch (256 entries)
     int rw, waves, cb, ns, cbs_max;
     int variant;            // kernel variant (0 simple, 1 pipelined, 2 + block prefetch)
-    int cbits;              // 24-bit indices: column bits (idx24_col_bits(rw))
+    int cbits;              // 24-bit indices and streamed lists: column bits
     int slab_begin[kMaxSlabs + 1];   // first column block of each slab
     size_t lds_bytes() const { return tiled_lds_bytes(waves, rw, cb, idx24 != 0); }
 };
@@ -162,11 +175,11 @@ size_t fused_lds_bytes(int tw, int th, int Q);
 hipError_t launch_update_fused(const FusedUpdate &A, int grouping, int threads, hipStream_t st);
 
 // Launchers (all asynchronous on `st`).
-// Workgroups of the persistent launch (all resident at once); *what names the
-// call that failed.
-hipError_t persistent_grid(int variant, int threads, size_t lds, int *grid, const char **what);
+// Workgroups of the persistent launch (all resident at once); streamed: some scan
+// has streamed lists; *what names the call that failed.
+hipError_t persistent_grid(int variant, bool streamed, int threads, size_t lds, int *grid, const char **what);
 hipError_t launch_admm_persistent(const PersistentDev *D, const PersistentPlan &plan, size_t lds,
-                                  int threads, int variant, int grid, hipStream_t st);
+                                  int threads, int variant, bool streamed, int grid, hipStream_t st);
 hipError_t launch_tiled_batch(const BatchTile *tiles, int64_t n_tiles, const TileMap *maps,
                               const float *const *xs, float *const *parts, int waves, size_t lds,
                               int variant, int vt, hipStream_t st);

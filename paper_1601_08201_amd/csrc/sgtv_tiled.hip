@@ -10,6 +10,8 @@
 // nontemporal 16-byte loads.  Every row of a wave's accumulator range is hit
 // by at most one lane per instruction, so read-modify-write needs no atomics
 // and each sum has a fixed order.
+#include <type_traits>
+
 #include "sgtv_device.h"
 #include "sgtv_persistent.h"
 
@@ -108,6 +110,285 @@ __device__ __forceinline__ void tile_super24(const U4 A, const U4 B, const U4 C,
     window24<VT, 16>(e, av, xs, my, cbits);
 }
 
+// Pointers to device memory by type: through a generic pointer (one that came
+// out of memory, as in the batched launches) accesses are flat loads, which
+// count as LDS accesses too, so every wait for LDS would wait for them.
+template <class T> using Global = __attribute__((address_space(1))) T *;
+typedef Global<const char> GlobalBytes;
+template <class T, bool KNOWN> struct DeviceOr { typedef Global<T> P; };
+template <class T> struct DeviceOr<T, false> { typedef T *P; };
+
+// The same for arrays that nothing writes while the kernel runs: uniform reads
+// become scalar loads.
+typedef const __attribute__((address_space(4))) int32_t *ConstInts;
+
+// The sums of a row block (n slots in LDS) to its rows row0 .. of out, slot[i]
+// (null: i) holding row row0 + i.  The slots of eight rows per thread are read
+// together (N): one after the other, their latency would be paid for every 1024
+// rows of the tile (3 to 4 us a launch).  The persistent walk has no registers
+// for it.
+template <int N>
+__device__ __forceinline__ void store_rows(const float *sums, int n, int64_t row0, int64_t n_rows, float *part,
+                                           const uint16_t *slot) {
+    const int rows = n_rows - row0 < n ? static_cast<int>(n_rows - row0) : n;
+    const int nthr = blockDim.x;
+    const Global<float> out = (Global<float>)(part + row0);
+    const Global<const uint16_t> sl = (Global<const uint16_t>)slot;
+    for (int i0 = threadIdx.x; i0 < rows; i0 += N * nthr) {
+        int at[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const int i = i0 + k * nthr < rows ? i0 + k * nthr : i0;
+            at[k] = slot ? static_cast<int>(sl[i]) : i;
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            if (i0 + k * nthr < rows) out[i0 + k * nthr] = sums[at[k]];
+    }
+}
+
+// ---------------------------------------------------------------- streamed lists
+// Product over streamed lists (TileMap::idx24 == kIdxStream).  The lists of
+// one wave in one tile follow each other without gaps, as one stream of
+// groups (one entry per lane) stored in chunks of kChunk groups: a 16-byte
+// plane of 8 two-byte indices per lane and the values as one (16-bit) or two
+// (FP32) 16-byte planes.  An index is delta << CB | column: the entries of a
+// lane are in row order, each list starts at the lane's base row, and delta
+// moves on to the entry's row (0: the row of the entry before).  No other
+// lane touches the rows between a lane's first and last; a step too wide for
+// delta passes through padding entries (value 0, column code cb: a zero in
+// LDS).  A lane without entries has its base at a spare zero beside it.
+//
+// A wave keeps DEPTH chunks in flight whatever list they belong to, so its
+// loads go on across the block barriers, which only hold back the use of
+// entries.
+//
+// Bound, on 128 x 128 x 128 with 64 entries per column (134 M entries): FP32
+// values by HBM, 152 us a product = 5.7 TB/s of its own bytes (24-bit lists,
+// 7 bytes an entry, one list at a time: 182 us); 16-bit values with half the
+// entries by the column blocks, 103 us (124): LDS is active half the time (6.7
+// cycles an access, 4 of them bank conflicts) and about 1.2 us of every block go
+// to the barriers and the staging.  A deeper ring does not fit 128 registers.
+constexpr int kChunk = kStreamChunk;
+
+template <int VT> struct ChunkValues;
+template <> struct ChunkValues<0> {
+    v4f a, b;
+    __device__ __forceinline__ void load(GlobalBytes val, int64_t chunk, uint32_t l16) {
+        const GlobalBytes p = val + chunk * (32 * kWave);
+        a = __builtin_nontemporal_load((Global<const v4f>)(p + l16));
+        b = __builtin_nontemporal_load((Global<const v4f>)(p + 16 * kWave + l16));
+    }
+    __device__ __forceinline__ float get(int i) const { return i < 4 ? a[i & 3] : b[i & 3]; }
+};
+template <int VT> struct ChunkValues16 {
+    v4u a;
+    __device__ __forceinline__ void load(GlobalBytes val, int64_t chunk, uint32_t l16) {
+        a = __builtin_nontemporal_load((Global<const v4u>)(val + chunk * (16 * kWave) + l16));
+    }
+    __device__ __forceinline__ float get(int i) const {
+        return Code<VT>::dec(static_cast<unsigned short>(i & 1 ? a[i >> 1] >> 16 : a[i >> 1] & 0xFFFFu));
+    }
+};
+template <> struct ChunkValues<1> : ChunkValues16<1> {};
+template <> struct ChunkValues<2> : ChunkValues16<2> {};
+
+template <int VT>
+struct Chunk {
+    v4u idx;
+    ChunkValues<VT> val;
+    __device__ __forceinline__ uint32_t code(int i) const { return i & 1 ? idx[i >> 1] >> 16 : idx[i >> 1] & 0xFFFFu; }
+};
+
+// Entries lo .. hi - 1 of a chunk (uniform bounds; FULL: all of them): every
+// gather and accumulator read is issued before the first addition, then the
+// running sum of a row goes on in a register while delta is 0.  row: index of
+// the lane's current row in LDS.
+template <int VT, int CB, bool FULL>
+__device__ __forceinline__ void stream_window(const Chunk<VT> &C, int lo, int hi, const float *xs, float *lds,
+                                              uint32_t &row) {
+    float t[kChunk], m[kChunk];
+    uint32_t r[kChunk];
+#pragma unroll
+    for (int i = 0; i < kChunk; ++i)
+        if (FULL || (i >= lo && i < hi)) {
+            const uint32_t e = C.code(i);
+            t[i] = xs[e & ((1u << CB) - 1u)];
+            row += e >> CB;
+            r[i] = row;
+            m[i] = lds[row];
+        }
+    float run = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kChunk; ++i)
+        if (FULL || (i >= lo && i < hi)) {
+            const bool cont = i > 0 && (FULL || i > lo) && (C.code(i) >> CB) == 0;
+            run = fmaf(C.val.get(i), t[i], cont ? run : m[i]);
+            lds[r[i]] = run;
+        }
+}
+
+// What a streamed tile needs of its map.
+struct StreamTile {
+    int tile, rb, slab, waves, rw, cb, cbs_max, cb0, ncbs;
+    int64_t n_rows, n_cols, bases;
+    const uint16_t *slot;          // of this tile
+};
+
+template <class Map>   // TileMap or its like in constant memory
+__device__ __forceinline__ StreamTile stream_tile(const Map &M, int tile) {
+    StreamTile T;
+    T.tile = tile;
+    T.rb = tile / M.ns;
+    T.slab = tile - T.rb * M.ns;
+    T.waves = M.waves;
+    T.rw = M.rw;
+    T.cb = M.cb;
+    T.cbs_max = M.cbs_max;
+    T.cb0 = M.slab_begin[T.slab];
+    T.ncbs = M.slab_begin[T.slab + 1] - T.cb0;   // at least 1
+    T.n_rows = M.n_rows;
+    T.n_cols = M.n_cols;
+    T.bases = M.pad;
+    T.slot = M.slot ? M.slot + static_cast<int64_t>(tile) * (T.waves * T.rw) : nullptr;
+    return T;
+}
+
+template <int VT, int CB, int XP, int DEPTH>
+__device__ __forceinline__ void stream_body(const StreamTile M, const int32_t *pk_, const void *val_,
+                                            const int32_t *goff_, const int32_t *poff_, const float *x_,
+                                            float *part) {
+    extern __shared__ float lds[];
+    const ConstInts goff = (ConstInts)goff_, poff = (ConstInts)poff_;
+    const GlobalBytes pk = (GlobalBytes)pk_, val = (GlobalBytes)val_;
+    const Global<const float> x = (Global<const float>)x_;
+    const int acc_floats = (M.waves * M.rw + 3) / 4 * 4;
+    float *xs = lds + acc_floats;
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lane = tid & (kWave - 1);
+    const int tile = M.tile, cb0 = M.cb0, ncbs = M.ncbs;
+
+    // the first chunks of the wave's stream, in flight while the block is staged
+    const int64_t c0 = poff[tile * M.waves + w];   // tiles x waves is an int: poff counts them
+    const int n_chunks = poff[tile * M.waves + w + 1] - static_cast<int>(c0);
+    const int last = n_chunks > 0 ? n_chunks - 1 : 0;   // an empty stream reads the spare chunk
+    const uint32_t l16 = static_cast<uint32_t>(lane) * 16u;
+    Chunk<VT> buf[DEPTH];
+    auto load = [&](Chunk<VT> &C, int k) {
+        const int64_t ch = c0 + (k < last ? k : last);
+        C.idx = __builtin_nontemporal_load((Global<const v4u>)(pk + ch * (16 * kWave) + l16));
+        C.val.load(val, ch, l16);
+    };
+#pragma unroll
+    for (int u = 0; u + 1 < DEPTH; ++u) load(buf[u], u);
+
+    // list ends (groups of the stream) and base rows, one list ahead
+    const int64_t list0 = static_cast<int64_t>(tile) * M.cbs_max * M.waves + w;
+    const GlobalBytes bases = (GlobalBytes)(poff_ + M.bases);
+    auto base_of = [&](int64_t L) {
+        return static_cast<uint32_t>(
+            *(Global<const uint16_t>)(bases + L * (2 * kWave) + static_cast<uint32_t>(lane) * 2u));
+    };
+    auto list_of = [&](int c) { return list0 + static_cast<int64_t>(c < ncbs ? c : ncbs - 1) * M.waves; };
+    int lend = 0, next_end = 0;
+    uint32_t row = 0, next_base = 0;
+    v4f xr[XP];
+    // column block c of the slab (the last one again past the end); a chunk past
+    // a narrow block reads the block's first float4
+    const uint32_t t16 = static_cast<uint32_t>(tid) * 16u;
+    auto block_bytes = [&](int c) {
+        const int64_t rem = M.n_cols - static_cast<int64_t>(cb0 + c) * M.cb;
+        return static_cast<uint32_t>(rem < M.cb ? static_cast<int>(rem) : M.cb) * 4u;
+    };
+    auto load_x = [&](int c) {
+        c = c < ncbs ? c : ncbs - 1;
+        const GlobalBytes src = (GlobalBytes)(x + static_cast<int64_t>(cb0 + c) * M.cb);
+        const uint32_t n = block_bytes(c);
+#pragma unroll
+        for (int k = 0; k < XP; ++k) {
+            const uint32_t o = t16 + static_cast<uint32_t>(k * nthr) * 16u;
+            xr[k] = *(Global<const v4f>)(src + (o < n ? o : 0u));
+        }
+    };
+    auto store_x = [&](int c) {
+        const uint32_t n = block_bytes(c);
+#pragma unroll
+        for (int k = 0; k < XP; ++k) {
+            const uint32_t o = t16 + static_cast<uint32_t>(k * nthr) * 16u;
+            if (o < n) *reinterpret_cast<v4f *>(reinterpret_cast<char *>(xs) + o) = xr[k];
+        }
+    };
+    const uint32_t my = static_cast<uint32_t>(w * M.rw);
+    load_x(0);
+    lend = goff[list0];
+    row = my + base_of(list0);
+    for (int i = tid * 4; i < acc_floats; i += nthr * 4) *reinterpret_cast<v4f *>(lds + i) = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    if (tid < 4) xs[M.cb + tid] = 0.0f;   // the zero slot, and the spare of lanes without entries
+    store_x(0);
+    load_x(1);
+    next_end = goff[list_of(1)];
+    next_base = base_of(list_of(1));
+    load(buf[DEPTH - 1], DEPTH - 1);   // after these reads, as in every later step
+    __syncthreads();
+
+    // The wave is done with block c: on to the next.  After the last one no list
+    // ends any more (the rest of the last chunk is padding).  No step reports
+    // the end to the loop below: its length is known beforehand, and an exit
+    // from between the loads would make the compiler wait for all of them.
+    int c = 0;
+    auto advance = [&]() {
+        if (++c < ncbs) {
+            __syncthreads();   // every wave is done with the staged block
+            store_x(c);
+            lend = __builtin_amdgcn_readfirstlane(next_end);
+            row = my + next_base;
+            __syncthreads();
+            load_x(c + 1);
+            next_end = goff[list_of(c + 1)];
+            next_base = base_of(list_of(c + 1));
+        } else {
+            lend = 0x7FFFFFFF;
+        }
+    };
+    // The first list that ends in a chunk was begun in an earlier one, so at
+    // least one chunk load has been issued since the reads of the next block and
+    // base rows: the wait for them leaves that load in flight.  A further list
+    // in the same chunk was not, and is kept off that path: it waits for all.
+    auto step = [&](const Chunk<VT> &C, int k) {
+        const int k8 = k * kChunk;
+        int lo = 0;
+        if (lend <= k8 + kChunk) {   // the list ends within this chunk
+            lo = lend - k8;
+            if (lo > 0) stream_window<VT, CB, false>(C, 0, lo, xs, lds, row);
+            advance();
+            while (lend <= k8 + kChunk) {
+#pragma unroll
+                for (int q = 0; q < XP; ++q) asm volatile("" ::"v"(xr[q]));
+                asm volatile("" ::"v"(next_base));
+                const int hi = lend - k8;
+                if (hi > lo) stream_window<VT, CB, false>(C, lo, hi, xs, lds, row);
+                lo = hi;
+                advance();
+            }
+        }
+        if (lo == 0) stream_window<VT, CB, true>(C, 0, kChunk, xs, lds, row);
+        else if (lo < kChunk) stream_window<VT, CB, false>(C, lo, kChunk, xs, lds, row);
+    };
+    for (int k = 0; k < n_chunks; k += DEPTH)
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) {
+            if (k + u < n_chunks) step(buf[u], k + u);
+            load(buf[u], k + u + DEPTH);
+        }
+    // a wave without entries (or with none in the last blocks) still keeps the
+    // others company at the barriers of the blocks
+    while (c + 1 < ncbs) advance();
+    __syncthreads();
+    store_rows<DEPTH == 1 ? 1 : 8>(lds, M.waves * M.rw, static_cast<int64_t>(M.rb) * (M.waves * M.rw), M.n_rows,
+               part + static_cast<int64_t>(M.slab) * M.n_rows, M.slot);
+}
+
 // MODE 0: one batch at a time, the next column block staged after the
 //         barrier; 32-bit or 24-bit indices.
 // MODE 1: two batches in flight per wave (the batch past the end of a list is
@@ -118,14 +399,29 @@ __device__ __forceinline__ void tile_super24(const U4 A, const U4 B, const U4 C,
 //         of the current block has been issued.
 template <int VT, int MODE, bool PREFETCH = true>
 __device__ __forceinline__ void tiled_body(const TileMap &M, int64_t tile,
-                                           const int32_t *__restrict__ pk,
-                                           const typename Code<VT>::T *__restrict__ val,
-                                           const int32_t *__restrict__ goff,
-                                           const int32_t *__restrict__ poff,
-                                           const float *__restrict__ x,
+                                           const int32_t *__restrict__ pk_,
+                                           const typename Code<VT>::T *__restrict__ val_,
+                                           const int32_t *__restrict__ goff_,
+                                           const int32_t *__restrict__ poff_,
+                                           const float *__restrict__ x_,
                                            float *__restrict__ part) {
     typedef typename Code<VT>::T T;
     typedef typename Code<VT>::V4 V4;
+    // the persistent walk (no PREFETCH) keeps generic pointers: with these it spills more
+    typedef typename DeviceOr<const int32_t, PREFETCH>::P PInt;
+    typedef typename DeviceOr<const T, PREFETCH>::P PVal;
+    typedef typename DeviceOr<const float, PREFETCH>::P PFlt;
+    typedef typename DeviceOr<const v4i, PREFETCH>::P PI4;
+    typedef typename DeviceOr<const V4, PREFETCH>::P PV4;
+    typedef typename DeviceOr<const v4f, PREFETCH>::P PF4;
+    typedef typename DeviceOr<const uint32_t, PREFETCH>::P PU;
+    typedef typename DeviceOr<const v4u, PREFETCH>::P PU4;
+    typedef typename DeviceOr<const v2u, PREFETCH>::P PU2;
+    const PInt pk = (PInt)pk_;
+    const PVal val = (PVal)val_;
+    const PFlt x = (PFlt)x_;
+    typedef typename std::conditional<PREFETCH, ConstInts, const int32_t *>::type Ints;
+    const Ints goff = (Ints)goff_, poff = (Ints)poff_;
     extern __shared__ float lds[];
     // row sums: rw per wave, plus the padding row of the 32-bit format
     const int rw1 = M.rw + (M.idx24 ? 0 : 1);
@@ -151,8 +447,8 @@ __device__ __forceinline__ void tiled_body(const TileMap &M, int64_t tile,
     const int cb0 = M.slab_begin[slab];
     const int ncbs = M.slab_begin[slab + 1] - cb0;
     const int64_t list0 = ((rb * M.ns + slab) * M.cbs_max) * M.waves + w;
-    const v4i *pad4 = reinterpret_cast<const v4i *>(pk + M.pad) + lane;
-    const V4 *padv4 = reinterpret_cast<const V4 *>(val + M.pad) + lane;
+    const PI4 pad4 = (PI4)(pk + M.pad) + lane;
+    const PV4 padv4 = (PV4)(val + M.pad) + lane;
 
     // the gathered vector is padded to a multiple of 4 floats plus 16, so a
     // whole float4 that starts inside it stays inside the allocation
@@ -161,7 +457,7 @@ __device__ __forceinline__ void tiled_body(const TileMap &M, int64_t tile,
         const int64_t rem = M.n_cols - col0;
         const int ncols = rem < M.cb ? static_cast<int>(rem) : M.cb;
         for (int i4 = tid * 4; i4 < ncols; i4 += nthr * 4)
-            *reinterpret_cast<v4f *>(xs + i4) = *reinterpret_cast<const v4f *>(x + col0 + i4);
+            *reinterpret_cast<v4f *>(xs + i4) = *(PF4)(x + col0 + i4);
     }
     __syncthreads();
 
@@ -178,7 +474,7 @@ __device__ __forceinline__ void tiled_body(const TileMap &M, int64_t tile,
     // workgroup would wait for them at once with nothing else in flight.
     // The reads are unconditional (the last block rereads its own list;
     // 32-bit lists read goff in place of poff and ignore the value).
-    const int32_t *lp = M.idx24 ? poff : goff;
+    const Ints lp = M.idx24 ? poff : goff;
     int nx_g0 = 0, nx_g1 = 0, nx_po = 0;
     if (ncbs > 0) {
         nx_g0 = goff[list0];
@@ -198,8 +494,8 @@ __device__ __forceinline__ void tiled_body(const TileMap &M, int64_t tile,
         }
         const int nb4 = ng >> 2;
         const int64_t base = static_cast<int64_t>(g0) * kWave;
-        const v4i *p4 = reinterpret_cast<const v4i *>(pk + base) + lane;
-        const V4 *v4 = reinterpret_cast<const V4 *>(val + base) + lane;
+        const PI4 p4 = (PI4)(pk + base) + lane;
+        const PV4 v4 = (PV4)(val + base) + lane;
 
         const int cn = c + 1 < ncbs ? c + 1 : c;
         const int64_t ncol0 = static_cast<int64_t>(cb0 + cn) * M.cb;
@@ -207,11 +503,10 @@ __device__ __forceinline__ void tiled_body(const TileMap &M, int64_t tile,
         const int nncols = nrem < M.cb ? static_cast<int>(nrem) : M.cb;
         v4f xr[kXPrefetch];
         const bool i24 = MODE == 0 && M.idx24;
-        const uint32_t *p3 = nullptr;
-        if (i24) p3 = reinterpret_cast<const uint32_t *>(pk + po);
+        const PU p3 = (PU)(pk + (i24 ? po : 0));
         if (MODE == 0 && i24) {
             const int nsb = nb4 >> 2;
-            const v4u *qs = reinterpret_cast<const v4u *>(p3) + lane;
+            const PU4 qs = (PU4)p3 + lane;
             for (int sb = 0; sb < nsb; ++sb) {
                 const v4u A = __builtin_nontemporal_load(qs + sb * 3 * kWave);
                 const v4u B = __builtin_nontemporal_load(qs + sb * 3 * kWave + kWave);
@@ -222,9 +517,9 @@ __device__ __forceinline__ void tiled_body(const TileMap &M, int64_t tile,
                 const V4 a3 = __builtin_nontemporal_load(v4 + (4 * sb + 3) * kWave);
                 tile_super24<VT>(A, B, C, a0, a1, a2, a3, xs, my, cbits);
             }
-            const uint32_t *q2 = p3 + static_cast<int64_t>(nsb) * 12 * kWave;
-            const v2u *qa = reinterpret_cast<const v2u *>(q2) + lane;
-            const uint32_t *qb = q2 + 2 * kWave + lane;
+            const PU q2 = p3 + static_cast<int64_t>(nsb) * 12 * kWave;
+            const PU2 qa = (PU2)q2 + lane;
+            const PU qb = q2 + 2 * kWave + lane;
             for (int b = nsb * 4; b < nb4; ++b) {
                 const int rb4 = b - nsb * 4;
                 const v2u w01 = __builtin_nontemporal_load(qa + rb4 * (3 * kWave / 2));
@@ -257,12 +552,12 @@ __device__ __forceinline__ void tiled_body(const TileMap &M, int64_t tile,
 #pragma unroll
             for (int k = 0; k < kXPrefetch; ++k) {
                 const int i4 = (k * nthr + tid) * 4;
-                xr[k] = *reinterpret_cast<const v4f *>(x + ncol0 + (i4 < nncols ? i4 : 0));
+                xr[k] = *(PF4)(x + ncol0 + (i4 < nncols ? i4 : 0));
             }
         }
         const int64_t tail = base + static_cast<int64_t>(nb4) * 4 * kWave + lane;
         if (i24) {
-            const uint32_t *pt = p3 + static_cast<int64_t>(nb4) * 3 * kWave + lane;
+            const PU pt = p3 + static_cast<int64_t>(nb4) * 3 * kWave + lane;
             for (int g = nb4 * 4; g < ng; ++g) {
                 const uint32_t p = __builtin_nontemporal_load(pt + (g - nb4 * 4) * kWave);
                 const T a = __builtin_nontemporal_load(val + tail + static_cast<int64_t>(g - nb4 * 4) * kWave);
@@ -288,7 +583,7 @@ __device__ __forceinline__ void tiled_body(const TileMap &M, int64_t tile,
                 }
             } else {
                 for (int i4 = tid * 4; i4 < nncols; i4 += nthr * 4)
-                    *reinterpret_cast<v4f *>(xs + i4) = *reinterpret_cast<const v4f *>(x + ncol0 + i4);
+                    *reinterpret_cast<v4f *>(xs + i4) = *(PF4)(x + ncol0 + i4);
             }
             __syncthreads();
         }
@@ -298,10 +593,52 @@ __device__ __forceinline__ void tiled_body(const TileMap &M, int64_t tile,
     const int64_t row0 = rb * rb_rows;
     float *out = part + static_cast<int64_t>(slab) * M.n_rows;
     const uint16_t *sl = M.slot ? M.slot + (rb * M.ns + slab) * rb_rows : nullptr;
+    if (PREFETCH && rw1 == M.rw) {
+        store_rows<8>(acc, static_cast<int>(rb_rows), row0, M.n_rows, out, sl);
+        return;
+    }
     for (int64_t i = tid; i < rb_rows && row0 + i < M.n_rows; i += nthr) {
         const int64_t s = sl ? static_cast<int64_t>(sl[i]) : i;
         out[row0 + i] = acc[(s / M.rw) * rw1 + (s % M.rw)];
     }
+}
+
+// One tile in the format of its copy.  MODE 0 to 2: tiled_body; 3 and 4:
+// streamed lists with 13 and 14 column bits (2 and 4 float4 of a column block
+// per thread; 3 chunks in flight, what fits 128 registers); kModeAny: 0, 3 or 4
+// as the map says (the scans of a batch need not agree).
+constexpr int kModeAny = 5;
+
+template <int VT, int MODE, bool PREFETCH = true>
+__device__ __forceinline__ void product_tile(const TileMap &M, int64_t tile, const int32_t *__restrict__ pk,
+                                             const typename Code<VT>::T *__restrict__ val,
+                                             const int32_t *__restrict__ goff, const int32_t *__restrict__ poff,
+                                             const float *__restrict__ x, float *__restrict__ part) {
+    static_assert(MODE != kModeAny, "product_any picks the format");
+    if (MODE == 3) stream_body<VT, 13, 2, 3>(stream_tile(M, static_cast<int>(tile)), pk, val, goff, poff, x, part);
+    else if (MODE == 4) stream_body<VT, 14, 4, 3>(stream_tile(M, static_cast<int>(tile)), pk, val, goff, poff, x, part);
+    else tiled_body<VT, MODE >= 3 ? 0 : MODE, PREFETCH>(M, tile, pk, val, goff, poff, x, part);
+}
+
+// One tile of a batch, whose maps lie in device memory that nothing writes
+// meanwhile.
+typedef const __attribute__((address_space(4))) TileMap ConstMap;
+
+template <int VT, int MODE, bool PREFETCH = true>
+__device__ __forceinline__ void product_any(const TileMap *map, int tile, const float *x, float *part) {
+    const ConstMap &C = *(ConstMap *)map;
+    if (MODE == kModeAny && C.idx24 == kIdxStream) {
+        const StreamTile T = stream_tile(C, tile);
+        constexpr int kDepth = PREFETCH ? 3 : 1;
+        if (C.cbits == 13) stream_body<VT, 13, 2, kDepth>(T, C.pk, C.val, C.goff, C.poff, x, part);
+        else stream_body<VT, 14, 4, kDepth>(T, C.pk, C.val, C.goff, C.poff, x, part);
+        return;
+    }
+    // a reference, not a copy: fields (and the slab table indexed at run time)
+    // are read with scalar loads instead of living in scratch memory
+    const TileMap &M = *map;
+    product_tile<VT, MODE == kModeAny ? 0 : MODE, PREFETCH>(
+        M, tile, M.pk, static_cast<const typename Code<VT>::T *>(M.val), M.goff, M.poff, x, part);
 }
 
 template <int VT, int MODE>
@@ -311,7 +648,7 @@ __global__ __launch_bounds__(1024) void k_tiled(TileMap M, const int32_t *__rest
                                                 const int32_t *__restrict__ poff,
                                                 const float *__restrict__ x,
                                                 float *__restrict__ part) {
-    tiled_body<VT, MODE>(M, blockIdx.x, pk, val, goff, poff, x, part);
+    product_tile<VT, MODE>(M, blockIdx.x, pk, val, goff, poff, x, part);
 }
 
 // Many scans in one launch: workgroup b runs tile tiles[b].local of scan
@@ -323,11 +660,7 @@ __global__ __launch_bounds__(1024) void k_tiled_batch(const BatchTile *__restric
                                                       float *const *__restrict__ parts) {
     const BatchTile bt = tiles[blockIdx.x];
     if (bt.local < 0) return;   // alignment filler: the whole workgroup leaves
-    // a reference, not a copy: fields (and the slab table indexed at run time)
-    // are read with scalar loads instead of living in scratch memory
-    const TileMap &M = maps[bt.scan];
-    tiled_body<VT, MODE>(M, bt.local, M.pk, static_cast<const typename Code<VT>::T *>(M.val),
-                         M.goff, M.poff, xs[bt.scan], parts[bt.scan]);
+    product_any<VT, MODE>(maps + bt.scan, bt.local, xs[bt.scan], parts[bt.scan]);
 }
 
 // ---------------------------------------------------------------- persistent batch
@@ -365,15 +698,14 @@ struct PersistentWork {
         const bool fwd = phase == kPhaseForward;
         const BatchTile bt = (fwd ? D.tiles_f : D.tiles_b)[t];
         if (bt.local < 0) return;   // alignment filler (uniform in the workgroup)
-        const TileMap &M = (fwd ? D.maps_f : D.maps_b)[bt.scan];
+        const TileMap *map = (fwd ? D.maps_f : D.maps_b) + bt.scan;
         const float *x = fwd ? (fc ? D.xs_f1 : D.xs_f0)[bt.scan] : D.xs_b[bt.scan];
         float *part = (fwd ? D.parts_f : D.parts_b)[bt.scan];
         // without the register prefetch of the next column block: its 16
         // registers would push the walk past the 128 of a 16-wave workgroup
         // (same sums in the same order, only the timing of the staging loads
         // differs).  grab() synchronised the workgroup before this tile.
-        tiled_body<0, MODE, false>(M, bt.local, M.pk, static_cast<const float *>(M.val), M.goff, M.poff, x,
-                                   part);
+        product_any<0, MODE, false>(map, bt.local, x, part);
     }
     __device__ __forceinline__ void blocks(int phase, int64_t first, int64_t stride, int64_t n, int fc, int vc) {
         const int q = threadIdx.x / kBlock, t = threadIdx.x % kBlock;
@@ -578,7 +910,7 @@ __global__ __launch_bounds__(1024) void k_tiled_ratio(TileMap M, const int32_t *
                                                       const float *__restrict__ x, float *part,
                                                       RatioEpilogue E, int vec) {
     extern __shared__ float lds[];
-    tiled_body<VT, MODE>(M, blockIdx.x, pk, val, goff, poff, x, part);
+    product_tile<VT, MODE>(M, blockIdx.x, pk, val, goff, poff, x, part);
     const int64_t rb = blockIdx.x / M.ns;
     if (!last_slab(E.count + rb, M.ns, reinterpret_cast<int *>(lds))) return;
     const int64_t rows = static_cast<int64_t>(M.waves) * M.rw, row0 = rb * rows;
@@ -622,7 +954,7 @@ __global__ __launch_bounds__(1024) void k_tiled_update(TileMap M, const int32_t 
                                                        const float *__restrict__ x, float *part,
                                                        UpdateEpilogue E) {
     extern __shared__ float lds[];
-    tiled_body<VT, MODE>(M, blockIdx.x, pk, val, goff, poff, x, part);
+    product_tile<VT, MODE>(M, blockIdx.x, pk, val, goff, poff, x, part);
     const int64_t rb = blockIdx.x / M.ns;
     if (!last_slab(E.count + rb, M.ns, reinterpret_cast<int *>(lds))) return;
     const int64_t rows = static_cast<int64_t>(M.waves) * M.rw, row0 = rb * rows;
@@ -685,6 +1017,9 @@ template <int VT, int EPI, int GROUPING, bool WFULL>
 static hipError_t launch_tiled_v(const TileMap &M, const float *x, float *part, const RatioEpilogue *R,
                                  const UpdateEpilogue *U, hipStream_t st) {
     const bool fits = M.cb <= kXPrefetch * 4 * M.waves * kWave;
+    if (M.idx24 == kIdxStream)
+        return M.cbits == 13 ? launch_tiled_t<VT, 3, EPI, GROUPING, WFULL>(M, x, part, R, U, st)
+                             : launch_tiled_t<VT, 4, EPI, GROUPING, WFULL>(M, x, part, R, U, st);
     if (M.variant == 1) return launch_tiled_t<VT, 1, EPI, GROUPING, WFULL>(M, x, part, R, U, st);
     if (M.variant == 2 && fits) return launch_tiled_t<VT, 2, EPI, GROUPING, WFULL>(M, x, part, R, U, st);
     return launch_tiled_t<VT, 0, EPI, GROUPING, WFULL>(M, x, part, R, U, st);
@@ -733,7 +1068,7 @@ static hipError_t launch_tiled_batch_v(const BatchTile *tiles, int64_t n_tiles, 
                                        const float *const *xs, float *const *parts, int waves, size_t lds,
                                        int variant, hipStream_t st) {
     if (variant == 1) return launch_tiled_batch_t<VT, 1>(tiles, n_tiles, maps, xs, parts, waves, lds, st);
-    return launch_tiled_batch_t<VT, 0>(tiles, n_tiles, maps, xs, parts, waves, lds, st);
+    return launch_tiled_batch_t<VT, kModeAny>(tiles, n_tiles, maps, xs, parts, waves, lds, st);
 }
 
 hipError_t launch_tiled_batch(const BatchTile *tiles, int64_t n_tiles, const TileMap *maps,
@@ -750,8 +1085,16 @@ static const void *persistent_fn() {
     return reinterpret_cast<const void *>(&k_admm_persistent<MODE>);
 }
 
-hipError_t persistent_grid(int variant, int threads, size_t lds, int *grid, const char **what) {
-    const void *fn = variant == 1 ? persistent_fn<1>() : persistent_fn<0>();
+// Batches without streamed scans keep the walk without their code, which costs
+// it registers (16 scans of 9 x 41 x 54: 102 against 117 us an iteration; 8
+// uneven scans, streamed: 1545 against 1982 us with 24-bit lists).
+static const void *persistent_kernel(int variant, bool streamed) {
+    if (variant == 1) return persistent_fn<1>();
+    return streamed ? persistent_fn<kModeAny>() : persistent_fn<0>();
+}
+
+hipError_t persistent_grid(int variant, bool streamed, int threads, size_t lds, int *grid, const char **what) {
+    const void *fn = persistent_kernel(variant, streamed);
     // the dynamic limit leaves room for the kernel's own static LDS (its barrier flag)
     auto raise = [](const void *f) {
         hipFuncAttributes at{};
@@ -762,9 +1105,11 @@ hipError_t persistent_grid(int variant, int threads, size_t lds, int *grid, cons
     };
     static const hipError_t r0 = raise(persistent_fn<0>());
     static const hipError_t r1 = raise(persistent_fn<1>());
+    static const hipError_t r2 = raise(persistent_fn<kModeAny>());
     *what = "hipFuncGetAttributes / hipFuncSetAttribute";
     if (r0 != hipSuccess) return r0;
     if (r1 != hipSuccess) return r1;
+    if (r2 != hipSuccess) return r2;
     int dev = 0, cus = 0, per_cu = 0;
     *what = "hipGetDevice";
     hipError_t e = hipGetDevice(&dev);
@@ -783,8 +1128,8 @@ hipError_t persistent_grid(int variant, int threads, size_t lds, int *grid, cons
 }
 
 hipError_t launch_admm_persistent(const PersistentDev *D, const PersistentPlan &plan, size_t lds,
-                                  int threads, int variant, int grid, hipStream_t st) {
-    const void *fn = variant == 1 ? persistent_fn<1>() : persistent_fn<0>();
+                                  int threads, int variant, bool streamed, int grid, hipStream_t st) {
+    const void *fn = persistent_kernel(variant, streamed);
     const PersistentDev *a0 = D;
     PersistentPlan a1 = plan;
     void *args[] = {&a0, &a1};

@@ -1,0 +1,90 @@
+"""Streamed lists of the tiled products against the FP64 oracle (image relative
+L2 <= 1e-5, the bound of the FP32 path; 16-bit values: the oracle on the
+dequantised matrix), and run twice bit for bit.  That every row sum is the one
+of the CSR rows, bit for bit, is checked on the host
+(tests/test_host_stream.py).
+
+Sizes sit at the edges: one row, row blocks and column blocks with remainders,
+blocks at the limits of 13 and 14 column bits, few waves, empty lists and
+streams, runs of one row longer than a chunk, steps wider than a delta."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(I, ny, nx, Q, per_col, seed, kind="even"):
+    rng = np.random.default_rng(seed)
+    J = ny * nx * Q
+    if kind == "runs":      # a few rows hold most entries
+        rows = np.where(rng.random((J, per_col)) < 0.6, rng.integers(0, 5, (J, per_col)),
+                        rng.integers(0, I, (J, per_col)))
+    elif kind == "gaps":    # entries in every 40th row and a band of columns only
+        rows = rng.integers(0, max(1, I // 40), (J, per_col)) * 40
+    else:
+        rows = rng.integers(0, I, (J, per_col))
+    cols = np.repeat(np.arange(J), per_col)
+    if kind == "gaps":
+        cols = cols % max(1, J // 7)
+    A = sp.csr_matrix((rng.random(J * per_col).astype(np.float32) + 0.01, (rows.ravel(), cols)), shape=(I, J))
+    y = rng.poisson(5.0, I).astype(np.float32)
+    return A, y, np.full(I, 0.1, np.float32)
+
+
+CASES = {
+    # name: (I, ny, nx, Q, per_col, kind, schedule)
+    "13 bits, full block": (30000, 9, 41, 54, 24, "even", dict(fwd_rows_per_wave=64, fwd_block_cols=4092,
+                                                              back_rows_per_wave=64, back_block_cols=8188,
+                                                              fwd_slabs=1, back_slabs=1)),
+    "14 bits, widest block": (50000, 11, 23, 140, 24, "even", dict(fwd_rows_per_wave=128, fwd_block_cols=12000,
+                                                                  back_rows_per_wave=100, back_block_cols=16380,
+                                                                  fwd_slabs=1, back_slabs=1)),
+    "all of the LDS": (60000, 16, 32, 64, 24, "even", dict(fwd_rows_per_wave=2048, fwd_block_cols=8188,
+                                                         back_rows_per_wave=1560, back_block_cols=15976,
+                                                         fwd_slabs=1, back_slabs=1)),
+    "narrow blocks, slabs": (3001, 7, 13, 33, 16, "even", dict(waves=4, fwd_rows_per_wave=65, fwd_block_cols=256,
+                                                             fwd_slabs=3, back_rows_per_wave=70,
+                                                             back_block_cols=128, back_slabs=5)),
+    "one wave": (700, 5, 6, 31, 9, "even", dict(waves=1, fwd_rows_per_wave=64, fwd_block_cols=512,
+                                              back_rows_per_wave=300, back_block_cols=100)),
+    "long runs": (2500, 6, 9, 40, 30, "runs", dict(waves=8, fwd_rows_per_wave=64, fwd_block_cols=1024,
+                                                 back_rows_per_wave=64, back_block_cols=2048)),
+    "wide steps": (9000, 6, 9, 40, 20, "gaps", dict(waves=8, fwd_rows_per_wave=1000, fwd_block_cols=4096,
+                                                  back_rows_per_wave=64, back_block_cols=4096)),
+    "one row": (1, 4, 4, 16, 1, "even", dict()),
+    "automatic": (131072, 16, 16, 64, 20, "even", dict()),
+}
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_streamed_matches_oracle(name, storage):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"   # before the library is loaded
+    import oracle
+    from paper_1601_08201_amd import sgtv
+    I, ny, nx, Q, per_col, kind, sched = CASES[name]
+    A, y, r = problem(I, ny, nx, Q, per_col, 3, kind)
+    rowptr = A.indptr.astype(np.int64)
+    out = []
+    for _ in range(2):
+        R = sgtv.Reconstructor(device=0)
+        if sched:
+            R.set_schedule(**sched)
+        R.set_system(I, ny, nx, Q, rowptr, A.indices, A.data, storage=storage)
+        R.set_data(y, r, 0.1, 1.0)
+        R.iterate(3)
+        out.append((R.image(),) + R.split())
+        R.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
+    p = SimpleNamespace(ny=ny, nx=nx, Q=Q, I=I, J=ny * nx * Q, rowptr=rowptr, col=A.indices, val=A.data, y=y, r=r,
+                        beta=0.1, rho=1.0, sweeps=1)
+    if storage != "f32":
+        p.val = oracle.quantise(p.col, p.val, p.J, storage)[2]
+    f = oracle.admm(p, 3, report=False)[0]
+    err = np.linalg.norm(out[0][0] - f) / np.linalg.norm(f)
+    print(name, storage, "rel_l2", err, flush=True)
+    assert err <= 1e-5
