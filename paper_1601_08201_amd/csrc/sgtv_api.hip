@@ -243,11 +243,39 @@ int64_t next_pow2(int64_t v) {
     return p;
 }
 
-// Automatic schedule: column blocks of up to 16380 entries, slabs so that one
-// slab of the gathered vector is at most 2 MiB (an XCD's 4 MiB L2 keeps it
-// next to the streamed entries), then more slabs and fewer rows per wave until
-// the grid has at least 256 workgroups (one per CU).
-TileParams choose_tiles(int64_t n_rows, int64_t n_cols, int waves, int rw, int cb, int ns) {
+// Modelled time in us of one product of a matrix of n_rows x n_cols with nnz
+// entries under schedule t, 16 waves, one workgroup per CU.  Fitted to 128^3
+// with 32 and 64 entries per column, 64^3 with 32 and 77 x 101 x 93 with 48
+// under 30 schedules (within about 10 %): a round of tiles costs 8 us, a column
+// block 0.64 us for its two barriers and 0.59 us per 16380 staged columns, a
+// group of every wave 0.17 us (a list has one group more than its share); the
+// entries of all tiles pass no faster than 5.8 TB/s; and every slab writes a
+// partial sum per row that the next kernel reads one after the other, at about
+// 5 TB/s and 0.12 us each.
+double modelled_us(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_bytes, const TileParams &t) {
+    constexpr double kCus = 256.0;
+    const double rb = static_cast<double>(t.waves) * t.rw;
+    const double tiles = std::ceil(n_rows / rb) * t.ns;
+    const double blocks = std::ceil(std::ceil(static_cast<double>(n_cols) / t.cb) / t.ns);
+    const double cols = std::min<double>(t.cb, static_cast<double>(n_cols));
+    const double entries = static_cast<double>(nnz) / n_rows / n_cols * std::min<double>(t.rw, static_cast<double>(n_rows)) * cols;
+    const double tile = 8.0 + blocks * (0.64 + 3.6e-5 * cols + 0.17 * (entries / 64.0 + 1.0));
+    const double stream = static_cast<double>(nnz) * (2.2 + value_bytes) / 5.8e6;
+    return std::max(std::ceil(tiles / kCus) * tile, stream) + t.ns * (0.12 + 8.0 * n_rows / 5.0e6);
+}
+
+// Automatic schedule: of the tile heights that fill whole rounds of the 256 CUs
+// (a tile more than a round's costs a whole round: 77 x 101 x 93 with 360 tiles
+// took 64 us a product, with 256 42 us), the column blocks and slab counts, the
+// fastest by the model above.  Of equally fast ones the first: wide blocks and
+// few slabs.  The rule below stays for heights that are given (a batch's scans
+// fill the GPU together) and other workgroup sizes than the fitted one, and below
+// 2 M entries, where every schedule costs about as much and the model's many
+// slabs cost a batch more (9 x 41 x 54 alone 24.0 against 24.4 us an iteration,
+// 16 such scans in a batch 133 against 58 us): one slab of the gathered vector is
+// at most 2 MiB, so an XCD's 4 MiB L2 keeps it next to the streamed entries.
+TileParams choose_tiles(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_bytes, int waves, int rw, int cb,
+                        int ns) {
     TileParams t;
     t.waves = waves > 0 ? waves : 16;
     // 16380 = the widest block of the 24-bit index format (a multiple of 4
@@ -261,22 +289,49 @@ TileParams choose_tiles(int64_t n_rows, int64_t n_cols, int waves, int rw, int c
         t.ns = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({want, 8, ncb})));
     }
     if (t.ns > ncb) t.ns = static_cast<int>(std::max<int64_t>(1, ncb));
-    if (rw > 0) {
-        t.rw = rw;
-    } else {
-        // until there is a tile for every CU: more slabs first (up to 8, each
-        // slab keeps its XCDs and its slice of the vector in L2), then shorter
-        // tiles (long lists keep the packing dense)
-        int r = 1024;
-        auto tiles = [&](int rr) { return ((n_rows + int64_t(t.waves) * rr - 1) / (int64_t(t.waves) * rr)) * t.ns; };
-        while (tiles(r) < 256) {
-            if (ns <= 0 && t.ns < 8 && 2 * t.ns <= ncb) t.ns *= 2;
-            else if (r > 64) r >>= 1;
-            else break;
+    t.rw = rw > 0 ? rw : 64;
+    if (rw > 0 || nnz < (int64_t(1) << 21) || t.waves != 16) {
+        if (rw <= 0) {
+            // until there is a tile for every CU: more slabs first (up to 8), then
+            // shorter tiles (long lists keep the packing dense)
+            int r = 1024;
+            auto tiles = [&](int rr) { return ((n_rows + int64_t(t.waves) * rr - 1) / (int64_t(t.waves) * rr)) * t.ns; };
+            while (tiles(r) < 256) {
+                if (ns <= 0 && t.ns < 8 && 2 * t.ns <= ncb) t.ns *= 2;
+                else if (r > 64) r >>= 1;
+                else break;
+            }
+            t.rw = r;
         }
-        t.rw = r;
+        return t;
     }
-    return t;
+    TileParams best = t;
+    double best_us = 0.0;
+    for (const int widest : {16380, 15976, 12284, 8188, 4092})
+        for (int k = ns > 0 ? ns : 1; k <= (ns > 0 ? ns : sgtv::kMaxSlabs); ++k) {
+            // blocks of even width, as many in every slab
+            int64_t nb = std::max<int64_t>(1, (n_cols + widest - 1) / widest);
+            if (ns <= 0) nb = (nb + k - 1) / k * k;
+            const int cc = cb > 0 ? cb : static_cast<int>(std::max<int64_t>(4, ((n_cols + nb - 1) / nb + 3) / 4 * 4));
+            const int64_t blocks = std::max<int64_t>(1, (n_cols + cc - 1) / cc);
+            if (ns <= 0 && k > blocks) break;
+            const int slabs = static_cast<int>(std::min<int64_t>(k, blocks));
+            // room beside the block, with the spare rows of 32-bit lists
+            const int rw_max = std::min<int>(2048, (40960 - cc) / 16 - 1);
+            for (int rounds = 1; rounds <= 64; ++rounds) {
+                const int64_t n_rb = std::max<int64_t>(1, 256 * rounds / slabs);
+                const int64_t need = (n_rows + 16 * n_rb - 1) / (16 * n_rb);
+                if (need > rw_max) continue;
+                const TileParams q{static_cast<int>(std::max<int64_t>(64, need)), 16, cc, slabs};
+                const double us = modelled_us(n_rows, n_cols, nnz, value_bytes, q);
+                if (best_us == 0.0 || us < 0.99 * best_us) {
+                    best = q;
+                    best_us = us;
+                }
+                if (need <= 64 || rounds >= 4) break;
+            }
+        }
+    return best;
 }
 
 // LDS of a workgroup of the tiled product; idx24: the inner loop reads 24-bit
@@ -1365,8 +1420,9 @@ int pack_system(sgtv_ctx_s *c, Packed &PK, int64_t I, int32_t ny, int32_t nx, in
     S->sched = c->want;
     if (S->format == SGTV_FORMAT_TILED) {
         const sgtv_schedule &q = c->want;
-        const TileParams tf = choose_tiles(I, J, q.waves, q.fwd_rows_per_wave, q.fwd_block_cols, q.fwd_slabs);
-        const TileParams tb = choose_tiles(J, I, q.waves, q.back_rows_per_wave, q.back_block_cols, q.back_slabs);
+        const int vb = vt == SGTV_F32 ? 4 : 2;
+        const TileParams tf = choose_tiles(I, J, nnz, vb, q.waves, q.fwd_rows_per_wave, q.fwd_block_cols, q.fwd_slabs);
+        const TileParams tb = choose_tiles(J, I, nnz, vb, q.waves, q.back_rows_per_wave, q.back_block_cols, q.back_slabs);
         const bool var1 = q.variant <= 1;   // the simple loop, the only one on 24-bit indices
         if (tile_lds_bytes(tf, var1) > 163840 || tile_lds_bytes(tb, var1) > 163840)
             return fail(SGTV_EINVAL, "schedule needs more than 160 KiB of LDS per workgroup");
@@ -2689,7 +2745,7 @@ int64_t sgtv_workspace_bytes(int64_t I, int64_t J, int64_t nnz, int storage_dtyp
     // one column block) of E entries takes max(E / 64 + 1, longest row run)
     // groups of 64, the run estimated for rows with lam entries per block
     auto copy_bytes = [&](int64_t n_rows, int64_t n_cols, int64_t *slabs) -> double {
-        const TileParams t = choose_tiles(n_rows, n_cols, 16, 0, 0, 0);
+        const TileParams t = choose_tiles(n_rows, n_cols, nnz, static_cast<int>(vb), 16, 0, 0, 0);
         *slabs = t.ns;
         if (n_rows == 0 || n_cols == 0) return 0.0;
         const double n_rb = std::ceil(static_cast<double>(n_rows) / (16.0 * t.rw));
