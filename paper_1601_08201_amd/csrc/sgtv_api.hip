@@ -3458,8 +3458,6 @@ struct wsnet_s {
     DBuf dz[2];                                     // bf16 gradients w.r.t. pre-activations
     DBuf wpart, lpart, lred;
     DBuf lsum;                                      // FP64 sum of the training steps' losses and their count
-    DBuf xt, dt;                                    // weight gradient: X of every layer in three
-                                                    // shifted channel-major copies; dZ channel-major
     DBuf ipart, isum;                               // per-image FP64 sums (start images)
     int64_t step = 0;
     bool have_grad = false, have_params = false;
@@ -3467,7 +3465,7 @@ struct wsnet_s {
 
 namespace {
 
-constexpr int kLossBlocks = 4096;   // loss-gradient blocks (FP64 partial sums of the squared error)
+constexpr int kLossBlocks = 1024;   // loss-gradient blocks (FP64 partial sums of the squared error)
 constexpr int kImageBlocks = 64;    // partial sums per image (start images)
 
 __bf16 *bf(const DBuf &b, int64_t off = 0) { return b.as<__bf16>() + off; }
@@ -3480,37 +3478,37 @@ int net_weights(wsnet_s *n) {
     return SGTV_OK;
 }
 
-int net_stage(wsnet_s *n, DBuf &dst, const float *src, int64_t count, int mk) {
+bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+// Caller data as 16-byte aligned device memory: device arrays are read in place
+// by calls that wait for the device before they return, everything else is
+// copied to dst (a call that does not wait leaves the caller's array alone as
+// soon as the copy is done).
+int net_stage(wsnet_s *n, DBuf &dst, const float *src, int64_t count, int mk, bool waits, const float **p) {
+    if (waits && mk == SGTV_DEVICE && aligned16(src)) {
+        *p = src;
+        return SGTV_OK;
+    }
     HIP_TRY(hipMemcpyAsync(dst.p, src, sizeof(float) * count,
                            mk == SGTV_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, n->stream));
+    *p = dst.as<float>();
     return SGTV_OK;
 }
 
-// the layers, from the bf16 input already in the first activation buffer;
-// training: the hidden layers also write their outputs' shifted channel-major
-// copies for the weight gradients
-int net_layers(wsnet_s *n, int B, bool training = false) {
+// the layers, from the bf16 input already in the first activation buffer, to z
+// (training: the loss kernel forms softplus(z) itself) or to softplus(z) in out
+int net_layers(wsnet_s *n, int B, float *z, float *out) {
     const int64_t CK = static_cast<int64_t>(n->C) * 9 * n->C;
     for (int l = 0; l < n->L; ++l) {
         const float *bias = n->params.as<float>() + l * n->per_layer + CK;
         const __bf16 *X = bf(n->acts, l * n->max_batch * n->img);
         if (l + 1 < n->L)
-            HIP_TRY(sgtv::wsn::conv_relu(X, bf(n->wf, l * CK), bias, B, n->H, n->W,
-                                         bf(n->acts, (l + 1) * n->max_batch * n->img),
-                                         training ? bf(n->xt, (l + 1) * 3 * n->max_batch * n->img) : nullptr,
-                                         n->stream));
+            HIP_TRY(sgtv::wsn::conv_relu(X, bf(n->wf, l * CK), bias, B, n->H,
+                                         bf(n->acts, (l + 1) * n->max_batch * n->img), n->stream));
         else
-            // training: only z (the loss kernel forms softplus(z) itself)
-            HIP_TRY(sgtv::wsn::conv_softplus(X, bf(n->wf, l * CK), bias, B, n->H, n->W,
-                                             n->z_last.as<float>(), training ? nullptr : n->out.as<float>(),
-                                             n->stream));
+            HIP_TRY(sgtv::wsn::conv_softplus(X, bf(n->wf, l * CK), bias, B, n->H, z, out, n->stream));
     }
     return SGTV_OK;
-}
-
-int net_forward(wsnet_s *n, int B, bool training = false) {
-    HIP_TRY(sgtv::wsn::to_bf16(n->xin.as<float>(), bf(n->acts), B * n->img, n->stream));
-    return net_layers(n, B, training);
 }
 
 int net_check(wsnet_s *n, int B, int mk) {
@@ -3563,9 +3561,10 @@ int wsnet_create(wsnet *out, int device, void *hip_stream, int32_t layers, int32
         HIP_TRY(n->tgt.alloc(sizeof(float) * big));
         HIP_TRY(n->dz[0].alloc(2 * big));
         HIP_TRY(n->dz[1].alloc(2 * big));
-        HIP_TRY(n->wpart.alloc(sizeof(float) * (CK + channels) * max_batch * (height / sgtv::wsn::wgrad_rows(height))));
-        HIP_TRY(n->xt.alloc(2 * 3 * big * layers));
-        HIP_TRY(n->dt.alloc(2 * big));
+        int64_t wblocks = 0;   // a smaller batch may take more blocks than the largest
+        for (int32_t b = 1; b <= max_batch; ++b)
+            wblocks = std::max<int64_t>(wblocks, sgtv::wsn::wgrad_blocks(b, height));
+        HIP_TRY(n->wpart.alloc(sizeof(float) * (CK + channels) * wblocks));
         HIP_TRY(n->lpart.alloc(sizeof(double) * kLossBlocks));
         HIP_TRY(n->lred.alloc(sizeof(double) * 4));
         HIP_TRY(n->lsum.alloc(sizeof(double) * 2));
@@ -3668,9 +3667,13 @@ int wsnet_forward(wsnet net, const float *x_in, int32_t batch, float *x0, int me
     if (!x_in || !x0) return fail(SGTV_EINVAL, "null argument");
     DeviceGuard g(net->device);
     const int64_t cnt = batch * net->img;
-    if (int e = net_stage(net, net->xin, x_in, cnt, mem_kind)) return e;
-    if (int e = net_forward(net, batch)) return e;
-    HIP_TRY(hipMemcpyAsync(x0, net->out.p, sizeof(float) * cnt, to_caller(mem_kind), net->stream));
+    const float *x = nullptr;
+    if (int e = net_stage(net, net->xin, x_in, cnt, mem_kind, true, &x)) return e;
+    // the input has been read by the time the last layer writes: x0 may overlap it
+    float *out = mem_kind == SGTV_DEVICE && aligned16(x0) ? x0 : net->out.as<float>();
+    HIP_TRY(sgtv::wsn::to_bf16(x, bf(net->acts), cnt, net->stream));
+    if (int e = net_layers(net, batch, nullptr, out)) return e;
+    if (out != x0) HIP_TRY(hipMemcpyAsync(x0, out, sizeof(float) * cnt, to_caller(mem_kind), net->stream));
     HIP_TRY(hipStreamSynchronize(net->stream));
     return SGTV_OK;
 }
@@ -3684,17 +3687,20 @@ int wsnet_start(wsnet net, const float *f, int32_t batch, int mode, double c_out
     if (!(floor >= 0.0) || !std::isfinite(floor)) return fail(SGTV_EINVAL, "floor must be finite and >= 0");
     DeviceGuard g(net->device);
     const int64_t cnt = batch * net->img;
-    if (int e = net_stage(net, net->xin, f, cnt, mem_kind)) return e;
-    HIP_TRY(sgtv::wsn::image_partials(net->xin.as<float>(), net->img, batch, kImageBlocks,
-                                      net->ipart.as<double>(), net->stream));
+    const float *x = nullptr;
+    if (int e = net_stage(net, net->xin, f, cnt, mem_kind, true, &x)) return e;
+    HIP_TRY(sgtv::wsn::image_partials(x, net->img, batch, kImageBlocks, net->ipart.as<double>(), net->stream));
     HIP_TRY(sgtv::launch_reduce(net->ipart.as<double>(), kImageBlocks, batch, net->isum.as<double>(), net->stream));
-    HIP_TRY(sgtv::wsn::scale_to_bf16(net->xin.as<float>(), net->isum.as<double>(), net->img, cnt, bf(net->acts),
-                                     net->stream));
-    if (int e = net_layers(net, batch)) return e;
-    HIP_TRY(sgtv::wsn::start_image(net->xin.as<float>(), net->out.as<float>(), net->isum.as<double>(), net->img,
-                                   cnt, static_cast<float>(c_out), mode == WSNET_START_RATIO,
-                                   static_cast<float>(floor), net->tgt.as<float>(), net->stream));
-    HIP_TRY(hipMemcpyAsync(x0, net->tgt.p, sizeof(float) * cnt, to_caller(mem_kind), net->stream));
+    HIP_TRY(sgtv::wsn::scale_to_bf16(x, net->isum.as<double>(), net->img, batch, bf(net->acts), net->stream));
+    if (int e = net_layers(net, batch, nullptr, net->out.as<float>())) return e;
+    // f is read again beside x0's writes, value by value: x0 is written in place
+    // where it is f or apart from it
+    const bool apart = x0 + cnt <= x || x + cnt <= x0;
+    float *out = mem_kind == SGTV_DEVICE && aligned16(x0) && (x0 == x || apart) ? x0 : net->tgt.as<float>();
+    HIP_TRY(sgtv::wsn::start_image(x, net->out.as<float>(), net->isum.as<double>(), net->img, batch,
+                                   static_cast<float>(c_out), mode == WSNET_START_RATIO, static_cast<float>(floor), out,
+                                   net->stream));
+    if (out != x0) HIP_TRY(hipMemcpyAsync(x0, out, sizeof(float) * cnt, to_caller(mem_kind), net->stream));
     HIP_TRY(hipStreamSynchronize(net->stream));
     return SGTV_OK;
 }
@@ -3703,28 +3709,24 @@ int wsnet_start(wsnet net, const float *f, int32_t batch, int mode, double c_out
 
 namespace {
 
-// Forward and backward pass of a staged batch (inputs in xin, targets in
-// tgt): the gradient in grad, the summed squared error in lred[0]; nothing
-// waits for the device.
-int net_backward(wsnet_s *net, int32_t batch) {
+// Forward and backward pass of a batch on the device: the gradient in grad, the
+// summed squared error in lred[0]; nothing waits for the device.
+int net_backward(wsnet_s *net, int32_t batch, const float *x, const float *target) {
     const int64_t cnt = batch * net->img;
     const int64_t CK = static_cast<int64_t>(net->C) * 9 * net->C;
-    if (int e = net_forward(net, batch, true)) return e;
+    HIP_TRY(sgtv::wsn::to_bf16(x, bf(net->acts), cnt, net->stream));
+    if (int e = net_layers(net, batch, net->z_last.as<float>(), nullptr)) return e;
     int cur = 0;
-    HIP_TRY(sgtv::wsn::mse_grad(net->tgt.as<float>(), net->z_last.as<float>(), cnt, bf(net->dz[cur]),
-                                net->lpart.as<double>(), kLossBlocks, net->stream));
+    HIP_TRY(sgtv::wsn::mse_grad(target, net->z_last.as<float>(), cnt, bf(net->dz[cur]), net->lpart.as<double>(),
+                                kLossBlocks, net->stream));
     HIP_TRY(sgtv::launch_reduce(net->lpart.as<double>(), kLossBlocks, 1, net->lred.as<double>(), net->stream));
     for (int l = net->L - 1; l >= 0; --l) {
         const __bf16 *X = bf(net->acts, l * net->max_batch * net->img);
-        // the forward pass wrote X's shifted copies for every layer but the first, and
-        // below the last layer the backward-data convolution has written dZ channel-major
-        float *xt = reinterpret_cast<float *>(bf(net->xt, l * 3 * net->max_batch * net->img));
-        HIP_TRY(sgtv::wsn::conv_wgrad(X, bf(net->dz[cur]), batch, net->H, xt, net->dt.as<float>(),
-                                      net->wpart.as<float>(), net->grad.as<float>() + l * net->per_layer, l > 0,
-                                      l + 1 < net->L, net->stream));
+        HIP_TRY(sgtv::wsn::conv_wgrad(X, bf(net->dz[cur]), batch, net->H, net->wpart.as<float>(),
+                                      net->grad.as<float>() + l * net->per_layer, net->stream));
         if (l == 0) break;
-        HIP_TRY(sgtv::wsn::conv_masked(bf(net->dz[cur]), bf(net->wb, l * CK), batch, net->H, net->W, X,
-                                       bf(net->dz[cur ^ 1]), bf(net->dt), net->stream));
+        HIP_TRY(sgtv::wsn::conv_masked(bf(net->dz[cur]), bf(net->wb, l * CK), batch, net->H, X, bf(net->dz[cur ^ 1]),
+                                       net->stream));
         cur ^= 1;
     }
     net->have_grad = true;
@@ -3760,9 +3762,10 @@ int wsnet_backward(wsnet net, const float *x_in, const float *target, int32_t ba
     if (!x_in || !target) return fail(SGTV_EINVAL, "null argument");
     DeviceGuard g(net->device);
     const int64_t cnt = batch * net->img;
-    if (int e = net_stage(net, net->xin, x_in, cnt, mem_kind)) return e;
-    if (int e = net_stage(net, net->tgt, target, cnt, mem_kind)) return e;
-    if (int e = net_backward(net, batch)) return e;
+    const float *x = nullptr, *t = nullptr;
+    if (int e = net_stage(net, net->xin, x_in, cnt, mem_kind, true, &x)) return e;
+    if (int e = net_stage(net, net->tgt, target, cnt, mem_kind, true, &t)) return e;
+    if (int e = net_backward(net, batch, x, t)) return e;
     double h = 0.0;
     HIP_TRY(hipMemcpyAsync(&h, net->lred.p, sizeof(double), hipMemcpyDeviceToHost, net->stream));
     if (grad)
@@ -3787,9 +3790,10 @@ int wsnet_train_step(wsnet net, const float *x_in, const float *target, int32_t 
     if (int e = check_adam(lr, beta1, beta2, eps)) return e;
     DeviceGuard g(net->device);
     const int64_t cnt = batch * net->img;
-    if (int e = net_stage(net, net->xin, x_in, cnt, mem_kind)) return e;
-    if (int e = net_stage(net, net->tgt, target, cnt, mem_kind)) return e;
-    if (int e = net_backward(net, batch)) return e;
+    const float *x = nullptr, *t = nullptr;
+    if (int e = net_stage(net, net->xin, x_in, cnt, mem_kind, false, &x)) return e;
+    if (int e = net_stage(net, net->tgt, target, cnt, mem_kind, false, &t)) return e;
+    if (int e = net_backward(net, batch, x, t)) return e;
     HIP_TRY(sgtv::wsn::loss_accumulate(net->lred.as<double>(), static_cast<double>(cnt), net->lsum.as<double>(),
                                        net->stream));
     return net_adam(net, lr, beta1, beta2, eps);

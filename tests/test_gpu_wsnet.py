@@ -289,3 +289,61 @@ def test_train_step_equals_backward_and_adam(sg):
         B.train_step(xd, td, lr=-1.0)
     A.close()
     B.close()
+
+
+@pytest.mark.parametrize("B,H", [(32, 64), (32, 34), (16, 34), (4, 66), (1, 2)])
+def test_batch_equals_its_images(sg, B, H):
+    """Row splits of the convolutions (8, 4, 2, 1 rows a step; 34 and 66 leave
+    remainders) add every output in the same order: a batch gives the images of
+    single passes bit for bit.  The gradient of a batch of 2^k images is the mean
+    of theirs: the loss gradients differ by an exact power of two, so only FP32
+    sums in another grouping are compared (1e-5)."""
+    L = 2
+    p = layer_params(sg, L, 11)
+    x, t = (torch.from_numpy(a).cuda() for a in data(5, B=B, H=H))
+    N = sg.WarmStartNet(layers=L, height=H, max_batch=B).set_params(p)
+    full = N.forward(x)
+    one = torch.cat([N.forward(x[i:i + 1].clone()) for i in range(B)])
+    assert torch.equal(full, one)
+    g = torch.empty(N.n_params, device="cuda")
+    N.backward(x, t, g)
+    mean = torch.zeros(N.n_params, dtype=torch.float64, device="cuda")
+    gi = torch.empty_like(g)
+    for i in range(B):
+        N.backward(x[i:i + 1].clone(), t[i:i + 1].clone(), gi)
+        mean += gi.double() / B
+    err = float((g.double() - mean).norm() / mean.norm())
+    print("B", B, "H", H, "gradient against the mean of its images", err, flush=True)
+    assert err <= 1e-5
+    N.close()
+
+
+def test_device_arrays_in_place(sg):
+    """Device arrays are read and written in place; unaligned ones, outputs that
+    are the input or overlap it go another way to the same values, and inputs are
+    left as they were."""
+    B, H = 2, 8
+    p = layer_params(sg, 2, 7)
+    N = sg.WarmStartNet(layers=2, height=H, max_batch=B).set_params(p)
+    x, t = data(9, B=B, H=H)
+    n = x.size
+    host = {m: N.start(x, m, 1.5, floor=0.1) for m in ("ratio", "direct")}
+    hf = N.forward(x)
+    for off in (0, 1):
+        buf = torch.zeros(3 * n + 8, device="cuda")
+        xd = buf[off:off + n].view(x.shape)
+        xd.copy_(torch.from_numpy(x))
+        out = buf[n + 4 + off:2 * n + 4 + off].view(x.shape)
+        for m in host:
+            assert np.array_equal(N.start(xd, m, 1.5, out, 0.1).cpu().numpy(), host[m])
+        assert np.array_equal(N.forward(xd, out).cpu().numpy(), hf)
+        assert np.array_equal(xd.cpu().numpy(), x)
+    for shift in (0, 4, n // 2):   # the input itself, and buffers that overlap it
+        for m in list(host) + ["forward"]:
+            buf = torch.zeros(2 * n, device="cuda")
+            xd = buf[:n].view(x.shape)
+            xd.copy_(torch.from_numpy(x))
+            out = buf[shift:shift + n].view(x.shape)
+            got = N.forward(xd, out) if m == "forward" else N.start(xd, m, 1.5, out, 0.1)
+            assert np.array_equal(got.cpu().numpy(), hf if m == "forward" else host[m])
+    N.close()
