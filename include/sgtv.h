@@ -144,17 +144,18 @@ int sgtv_iterate(sgtv_ctx ctx, int n_iters);
 /* Capture and instantiate now the graph that sgtv_iterate(ctx, n_iters) would
  * replay from the current state, without running it, so that the next such
  * call only launches the graph (for callers that time or serve the iterations
- * and want the capture outside that call).  Leaves the state unchanged.  No
- * effect when graphs are off, kernel timing is on or n_iters < 2.  The graph
- * is dropped, like every captured graph, by calls that change the system,
- * data, parameters or state.  Errors: SGTV_EINVAL for n_iters < 0, SGTV_ESTATE
+ * and want the capture outside that call; long runs are pieces of one graph).
+ * Leaves the state unchanged.  No effect when graphs are off, kernel timing is
+ * on or n_iters < 2.  The graph is dropped, like every captured graph, by calls
+ * that change the system, parameters or state; new data with the same
+ * parameters (sgtv_set_data) keeps it.  Errors: SGTV_EINVAL for n_iters < 0, SGTV_ESTATE
  * before system and data are set, SGTV_EDEVICE if capture fails. */
 int sgtv_prepare(sgtv_ctx ctx, int n_iters);
 
 /* Graph replay of sgtv_iterate (default on): the launch sequence of n
- * iterations is captured once into a HIP graph per (n, buffer parity) and
+ * iterations is captured once into HIP graphs per (n, buffer parity) and
  * replayed on the context stream; captured graphs are dropped by every call
- * that changes the system, data, parameters or state.  enable = 0 launches
+ * that changes the system, parameters or state.  enable = 0 launches
  * the kernels one by one. */
 int sgtv_set_graphs(sgtv_ctx ctx, int enable);
 

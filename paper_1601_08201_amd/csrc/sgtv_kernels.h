@@ -255,6 +255,9 @@ hipError_t launch_split_from_state(const float *v, const float *a, float *d, flo
                                    const Grid &grid, int grouping, hipStream_t st);
 hipError_t launch_div_safe(const float *num, const float *den, float *out, int64_t n,
                            hipStream_t st);
+// first[0], first[1] (all ones before): smallest index of a y that is negative
+// or not finite, of an r that is not finite and positive
+hipError_t launch_check_data(const float *y, const float *r, int64_t n, uint32_t *first, hipStream_t st);
 hipError_t launch_check_range(const float *x, int64_t n, float lo, int strict_lo, float hi,
                               int *flag, hipStream_t st);
 

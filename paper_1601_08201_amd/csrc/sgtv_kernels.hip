@@ -315,6 +315,22 @@ __global__ void k_check_range(const float *__restrict__ x, int64_t n, float lo, 
     }
 }
 
+// Index of the first invalid count and background (n < 2^31); one atomic per
+// lane with an invalid value, none otherwise.
+__global__ __launch_bounds__(kBlock) void k_check_data(const float *__restrict__ y, const float *__restrict__ r,
+                                                       int64_t n, uint32_t *__restrict__ first) {
+    uint32_t by = 0xFFFFFFFFu, br = 0xFFFFFFFFu;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
+         i += static_cast<int64_t>(gridDim.x) * kBlock) {
+        const float yi = y[i], ri = r[i];
+        // false for NaN
+        if (!(yi >= 0.0f && yi <= 3.4028234664e38f)) by = min(by, static_cast<uint32_t>(i));
+        if (!(ri > 0.0f && ri <= 3.4028234664e38f)) br = min(br, static_cast<uint32_t>(i));
+    }
+    if (by != 0xFFFFFFFFu) atomicMin(first, by);
+    if (br != 0xFFFFFFFFu) atomicMin(first + 1, br);
+}
+
 // ---------------------------------------------------------------- launchers
 static inline unsigned blocks_for(int64_t n, int64_t per_block) {
     return static_cast<unsigned>((n + per_block - 1) / per_block);
@@ -476,6 +492,11 @@ hipError_t launch_div_safe(const float *num, const float *den, float *out, int64
                            hipStream_t st) {
     hipLaunchKernelGGL(k_div_safe, dim3(grid_stride_blocks(n)), dim3(kBlock), 0, st, num, den,
                        out, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_check_data(const float *y, const float *r, int64_t n, uint32_t *first, hipStream_t st) {
+    hipLaunchKernelGGL(k_check_data, dim3(grid_stride_blocks(n)), dim3(kBlock), 0, st, y, r, n, first);
     return hipGetLastError();
 }
 

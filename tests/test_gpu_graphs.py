@@ -90,3 +90,36 @@ def test_prepare_arguments(sg):
     np.testing.assert_array_equal(R.image(), E.image())
     R.close()
     E.close()
+
+
+def test_pieces_and_kept_graphs(sg):
+    """Past 80, iterations run in graph pieces of 40 and a rest, and graphs outlive
+    set_data with the same parameters: bit for bit the eager run, from host and
+    device arrays, after refused data, and past the graphs that are kept."""
+    import torch
+    prob = datagen.make_problem("small", 6)
+    other = datagen.make_problem("small", 7)
+    E = sg.Reconstructor().set_graphs(False).set_problem(prob)
+    G = sg.Reconstructor().set_problem(prob)
+    y2 = other.y * np.float32(1.5)
+    dev = [torch.from_numpy(a).cuda() for a in (y2, prob.r)]
+    bad = prob.y.copy()
+    bad[[7, 90]] = np.nan, -1.0
+    bad_r = prob.r.copy()
+    bad_r[5] = 0.0
+    for n in (39, 80, 81, 123, 2, 3, 4, 5, 6, 7, 8, 9, 120):
+        for R in (E, G):
+            R.set_data(prob.y, prob.r, prob.beta, prob.rho, 1)
+            R.iterate(n)
+            a = R.state()
+            with pytest.raises(sg.SgtvError, match="y has a negative or non-finite value at 7"):
+                R.set_data(bad, prob.r, prob.beta, prob.rho, 1)
+            with pytest.raises(sg.SgtvError, match="index 5"):
+                R.set_data(bad, bad_r, prob.beta, prob.rho, 1)
+            for u, v in zip(a[:3], R.state()[:3]):
+                np.testing.assert_array_equal(u, v)
+        np.testing.assert_array_equal(E.image(), G.image())
+        E.set_data(y2, prob.r, prob.beta, prob.rho, 1).iterate(n)
+        G.set_data(dev[0], dev[1], prob.beta, prob.rho, 1).iterate(n)
+        np.testing.assert_array_equal(E.image(), G.image())
+        assert E.objective() == G.objective()
