@@ -305,7 +305,7 @@ def test_batch_equals_its_images(sg, B, H):
     full = N.forward(x)
     one = torch.cat([N.forward(x[i:i + 1].clone()) for i in range(B)])
     assert torch.equal(full, one)
-    g = torch.empty(N.n_params, device="cuda")
+    g = torch.empty(N.n_params, dtype=torch.float32, device="cuda")
     N.backward(x, t, g)
     mean = torch.zeros(N.n_params, dtype=torch.float64, device="cuda")
     gi = torch.empty_like(g)
@@ -330,7 +330,7 @@ def test_device_arrays_in_place(sg):
     host = {m: N.start(x, m, 1.5, floor=0.1) for m in ("ratio", "direct")}
     hf = N.forward(x)
     for off in (0, 1):
-        buf = torch.zeros(3 * n + 8, device="cuda")
+        buf = torch.zeros(3 * n + 8, dtype=torch.float32, device="cuda")
         xd = buf[off:off + n].view(x.shape)
         xd.copy_(torch.from_numpy(x))
         out = buf[n + 4 + off:2 * n + 4 + off].view(x.shape)
@@ -340,7 +340,7 @@ def test_device_arrays_in_place(sg):
         assert np.array_equal(xd.cpu().numpy(), x)
     for shift in (0, 4, n // 2):   # the input itself, and buffers that overlap it
         for m in list(host) + ["forward"]:
-            buf = torch.zeros(2 * n, device="cuda")
+            buf = torch.zeros(2 * n, dtype=torch.float32, device="cuda")
             xd = buf[:n].view(x.shape)
             xd.copy_(torch.from_numpy(x))
             out = buf[shift:shift + n].view(x.shape)
