@@ -198,12 +198,15 @@ uint16_t to_f16(float x) {
     return u;
 }
 
+template <class Fn>
+void on_threads(int64_t n_items, Fn work);
+
 // Sliced-ELL packing of n lines given line pointers (CSR-like) into 64-line
 // slices, depth padded to a multiple of 4; see sgtv::Sell for the layout.
 template <class V>
 void pack_sell(int64_t n_lines, const std::vector<int64_t> &lptr, const std::vector<int32_t> &lidx,
                const std::vector<V> &lval, std::vector<int64_t> &sptr, std::vector<int32_t> &idx,
-               std::vector<V> &val) {
+               std::vector<V> &val, int32_t fill = 0) {
     const int64_t n_slices = (n_lines + sgtv::kSliceRows - 1) / sgtv::kSliceRows;
     sptr.assign(static_cast<size_t>(n_slices + 1), 0);
     for (int64_t k = 0; k < n_slices; ++k) {
@@ -213,9 +216,10 @@ void pack_sell(int64_t n_lines, const std::vector<int64_t> &lptr, const std::vec
         width = (width + 3) / 4 * 4;
         sptr[k + 1] = sptr[k] + width * 64;
     }
-    idx.assign(static_cast<size_t>(sptr[n_slices]), 0);
+    idx.assign(static_cast<size_t>(sptr[n_slices]), fill);
     val.assign(static_cast<size_t>(sptr[n_slices]), V(0));
-    for (int64_t k = 0; k < n_slices; ++k) {
+    on_threads(n_slices, [&](int64_t first, int64_t step) {
+        for (int64_t k = first; k < n_slices; k += step)
         for (int64_t l = k * 64; l < std::min(n_lines, (k + 1) * 64); ++l) {
             const int64_t lane = l - k * 64;
             for (int64_t t = 0; t < lptr[l + 1] - lptr[l]; ++t) {
@@ -224,7 +228,7 @@ void pack_sell(int64_t n_lines, const std::vector<int64_t> &lptr, const std::vec
                 val[pos] = lval[lptr[l] + t];
             }
         }
-    }
+    });
 }
 
 struct Tiled {
@@ -1098,12 +1102,14 @@ struct System {
     DBuf htab;                   // H0 by neighbour pattern (weights constant per direction)
     int fused_tw = 0, fused_th = 0;   // tile of the fused image and split update (0: not fused)
     int fused_threads = sgtv::kFusedThreads;
-    std::vector<int64_t> perm;   // internal row -> caller row (identity for tiles)
-    int64_t n_rslices = 0, n_cslices = 0;
+    std::vector<int64_t> perm;   // sliced-ELL line -> caller row (the tiles keep the caller's order)
+    int64_t n_rslices = 0, n_cslices = 0;   // of the sliced-ELL format, or of a small tiled scan's second copy
+    DBuf row_of;                 // small tiled scan: measurement of every line (perm)
     Tiled fwd, back;             // tiled format: A (rows = measurements), A^T (rows = voxels)
     DBuf fpart, bpart;           // per-slab partial sums
     DBuf fcount, bcount;         // arrival counters of the row-block epilogues (zero between launches)
 
+    bool small() const { return format == SGTV_FORMAT_TILED && n_rslices > 0; }
     sgtv::Sell rows() const {
         return {rs_ptr.as<int64_t>(), rs_idx.as<int32_t>(), rs_val.p, nullptr, I, n_rslices};
     }
@@ -1151,6 +1157,7 @@ struct sgtv_ctx_s {
     int device = 0;
     hipStream_t stream = nullptr;
     sgtv_schedule want{};        // requested schedule for the next system
+    bool in_batch = false;       // a batch's scan: it iterates on its tiles
     std::unique_ptr<System> sys;
     // data
     bool has_data = false;
@@ -1375,6 +1382,98 @@ void choose_fused_tile(int ny, int nx, int Q, int *tw, int *th) {
     *th = best_h;
 }
 
+// A scan whose iterations run on a second, sliced-ELL copy (launch_small_*):
+// the automatic schedule, fewer than 2.6 M entries, alone on the GPU.  us an
+// iteration against the tiles: 131 k entries 9.7 / 21.0, 478 k 13.5 / 25.0,
+// 1.1 M 15.2 / 33.1, 2.0 M 23.4 / 33.6, 2.4 M 25.9 / 29.4; 3.1 M 31.9 / 30.4,
+// 4.7 M 42.7 / 38.8.
+constexpr int64_t kSmallScan = int64_t(5) << 19;
+
+bool small_scan(const sgtv_ctx_s *c, int64_t I, int64_t J, int64_t nnz, const sgtv_schedule &q) {
+    return !c->in_batch && I < sgtv::kSmallPad && J < sgtv::kSmallPad && nnz > 0 && nnz < kSmallScan && q.waves == 0 && q.variant == 0 &&
+           q.fwd_rows_per_wave == 0 && q.fwd_block_cols == 0 && q.fwd_slabs == 0 && q.back_rows_per_wave == 0 &&
+           q.back_block_cols == 0 && q.back_slabs == 0;
+}
+
+// Longest line of a small scan's copy: one lane walks it alone.
+constexpr int64_t kSmallLine = 192;
+
+// The second copy of a small scan: lines of entries in the order in which the
+// tiled product of map M adds them (column block after column block), the first
+// entry of every slab but a line's first marked by kSmallCut in its index.
+// lines: the line of M at every position.  False: a line is too long.
+template <class V>
+bool pack_small_side(const sgtv::TileMap &M, const std::vector<int64_t> &lptr, const std::vector<int32_t> &lidx,
+                     const std::vector<V> &lval, const std::vector<int64_t> &lines, std::vector<int64_t> &sptr,
+                     std::vector<int32_t> &idx, std::vector<V> &val) {
+    const int64_t n = static_cast<int64_t>(lines.size());
+    std::vector<int64_t> ptr(static_cast<size_t>(n + 1), 0);
+    for (int64_t k = 0; k < n; ++k) {
+        const int64_t len = lptr[lines[k] + 1] - lptr[lines[k]];
+        if (len > kSmallLine) return false;
+        ptr[k + 1] = ptr[k] + len;
+    }
+    std::vector<int32_t> ii(lidx.size());
+    std::vector<V> vv(lval.size());
+    constexpr int64_t kPiece = 1024;
+    on_threads((n + kPiece - 1) / kPiece, [&](int64_t first, int64_t step) {
+        std::vector<int64_t> order;
+        for (int64_t piece = first; piece * kPiece < n; piece += step)
+            for (int64_t k = piece * kPiece; k < std::min(n, (piece + 1) * kPiece); ++k) {
+                const int64_t b = lptr[lines[k]], len = ptr[k + 1] - ptr[k];
+                order.resize(static_cast<size_t>(len));
+                bool sorted = true;
+                for (int64_t t = 0; t < len; ++t) {
+                    order[t] = b + t;
+                    sorted = sorted && (t == 0 || lidx[b + t - 1] / M.cb <= lidx[b + t] / M.cb);
+                }
+                if (!sorted)
+                    std::stable_sort(order.begin(), order.end(),
+                                     [&](int64_t x, int64_t y) { return lidx[x] / M.cb < lidx[y] / M.cb; });
+                int slab = 0;
+                for (int64_t t = 0; t < len; ++t) {
+                    const int32_t col = lidx[order[t]];
+                    const int was = slab;
+                    while (col / M.cb >= M.slab_begin[slab + 1]) ++slab;
+                    const bool cut = t > 0 && slab != was;
+                    ii[ptr[k] + t] = cut ? col | sgtv::kSmallCut : col;
+                    vv[ptr[k] + t] = lval[order[t]];
+                }
+            }
+    });
+    pack_sell(n, ptr, ii, vv, sptr, idx, val, sgtv::kSmallPad);
+    return true;
+}
+
+template <class V>
+void pack_small(Packed &PK, const std::vector<int64_t> &rp, const std::vector<int32_t> &ci, const std::vector<V> &av,
+                const std::vector<int64_t> &cp, const std::vector<int32_t> &cidx, const std::vector<V> &cv) {
+    System &S = *PK.S;
+    // rows by decreasing length (stable): the 64 rows of a slice have nearly equal ones
+    std::vector<int64_t> rows(static_cast<size_t>(S.I)), cols(static_cast<size_t>(S.J));
+    for (int64_t i = 0; i < S.I; ++i) rows[i] = i;
+    for (int64_t j = 0; j < S.J; ++j) cols[j] = j;
+    std::stable_sort(rows.begin(), rows.end(),
+                     [&](int64_t x, int64_t y) { return rp[x + 1] - rp[x] > rp[y + 1] - rp[y]; });
+    std::vector<V> rv, wv;
+    if (!pack_small_side(PK.fwd.map, rp, ci, av, rows, PK.rsp, PK.rsi, rv) ||
+        !pack_small_side(PK.back.map, cp, cidx, cv, cols, PK.csp, PK.csi, wv)) {
+        for (auto *v : {&PK.rsp, &PK.csp}) v->clear();
+        for (auto *v : {&PK.rsi, &PK.csi}) v->clear();
+        return;
+    }
+    S.n_rslices = static_cast<int64_t>(PK.rsp.size()) - 1;
+    S.n_cslices = static_cast<int64_t>(PK.csp.size()) - 1;
+    S.perm.swap(rows);
+    if constexpr (sizeof(V) == 4) {
+        PK.rsv32.swap(rv);
+        PK.csv32.swap(wv);
+    } else {
+        PK.rsv16.swap(rv);
+        PK.csv16.swap(wv);
+    }
+}
+
 // Validate the system and pack it on the host (no device memory touched).
 int pack_system(sgtv_ctx_s *c, Packed &PK, int64_t I, int32_t ny, int32_t nx, int32_t Q,
                 const int64_t *row_ptr, const int32_t *col_idx, const float *val, int64_t nnz, int vt,
@@ -1494,8 +1593,10 @@ int pack_system(sgtv_ctx_s *c, Packed &PK, int64_t I, int32_t ny, int32_t nx, in
         // transpose (rows ascending within a column) with the values alongside
         std::vector<int64_t> cp;
         std::vector<int32_t> cidx;
+        std::vector<float> cv32;
+        std::vector<uint16_t> cv16;
         if (vt == SGTV_F32) {
-            std::vector<float> cv;
+            std::vector<float> &cv = cv32;
             transpose_csr(I, J, rp, ci, av, cp, cidx, cv);
             clk.mark("transpose");
             if (int e = pack_tiled(PK.fwd, I, J, rp, ci, av, tf, i24)) return e;
@@ -1503,7 +1604,7 @@ int pack_system(sgtv_ctx_s *c, Packed &PK, int64_t I, int32_t ny, int32_t nx, in
             if (int e = pack_tiled(PK.back, J, I, cp, cidx, cv, tb, i24)) return e;
             clk.mark("back copy");
         } else {
-            std::vector<uint16_t> cv;
+            std::vector<uint16_t> &cv = cv16;
             transpose_csr(I, J, rp, ci, codes, cp, cidx, cv);
             clk.mark("transpose");
             if (int e = pack_tiled(PK.fwd, I, J, rp, ci, codes, tf, i24)) return e;
@@ -1515,6 +1616,10 @@ int pack_system(sgtv_ctx_s *c, Packed &PK, int64_t I, int32_t ny, int32_t nx, in
         PK.back.map.variant = S->sched.variant - 1;
         S->fwd.map = PK.fwd.map;
         S->back.map = PK.back.map;
+        if (small_scan(c, I, J, nnz, q)) {
+            if (vt == SGTV_F32) pack_small(PK, rp, ci, av, cp, cidx, cv32);
+            else pack_small(PK, rp, ci, codes, cp, cidx, cv16);
+        }
         PK.fpart_floats = static_cast<size_t>(I) * tf.ns;
         PK.bpart_floats = static_cast<size_t>(J) * tb.ns;
     } else {
@@ -1604,6 +1709,11 @@ int alloc_counters(sgtv_ctx_s *c, System &S) {
     return SGTV_OK;
 }
 
+int upload_row_of(System &S) {
+    HIP_TRY(upload(S.row_of, std::vector<int32_t>(S.perm.begin(), S.perm.end())));
+    return SGTV_OK;
+}
+
 // Put a packed system on the device: every buffer is allocated (from the
 // current arena, if any; a counting arena only adds up the bytes) and
 // filled, and the sensitivity s = A^T 1 is computed with the stored values
@@ -1618,7 +1728,8 @@ int upload_system(sgtv_ctx_s *c, Packed &PK, Arena *temp) {
         HIP_TRY(S.fpart.alloc(sizeof(float) * PK.fpart_floats));
         HIP_TRY(S.bpart.alloc(sizeof(float) * PK.bpart_floats));
         if (int e = alloc_counters(c, S)) return e;
-    } else {
+    }
+    if (S.format == SGTV_FORMAT_SELL || S.small()) {
         if (S.vt == SGTV_F32) {
             HIP_TRY(upload(S.rs_val, PK.rsv32));
             HIP_TRY(upload(S.cs_val, PK.csv32));
@@ -1630,6 +1741,8 @@ int upload_system(sgtv_ctx_s *c, Packed &PK, Arena *temp) {
         HIP_TRY(upload(S.rs_idx, PK.rsi));
         HIP_TRY(upload(S.cs_ptr, PK.csp));
         HIP_TRY(upload(S.cs_idx, PK.csi));
+        if (S.small())
+            if (int e = upload_row_of(S)) return e;
     }
     HIP_TRY(upload(S.H, PK.H));
     HIP_TRY(upload(S.htab, PK.htab));
@@ -1816,6 +1929,64 @@ int step(sgtv_ctx_s *c) {
                                       static_cast<float>(c->beta / c->rho), c->stream));
     c->vcur ^= 1;
     c->k += 1;
+    return SGTV_OK;
+}
+
+// n ADMM iterations as a launch sequence on the context stream.  On a small
+// scan's second copy the split update of an iteration shares a launch with the
+// next forward product; the last one has its own.  Kernel timing, the fused update
+// and the row-block epilogues keep to the tiles.
+int steps(sgtv_ctx_s *c, int n) {
+    const System &S = *c->sys;
+    if (!S.small() || c->profiling || c->epilogues || c->fused) {
+        for (int it = 0; it < n; ++it)
+            if (int e = step(c)) return e;
+        return SGTV_OK;
+    }
+    const float thr = static_cast<float>(c->beta / c->rho);
+    auto split = [&]() {
+        sgtv::SmallSplit P{};
+        P.f = c->f[c->fcur].as<float>();
+        P.v_old = c->v[c->vcur].as<float>();
+        P.a_old = c->a[c->vcur].as<float>();
+        P.v_new = c->v[c->vcur ^ 1].as<float>();
+        P.a_new = c->a[c->vcur ^ 1].as<float>();
+        P.grid = S.grid;
+        P.wts = S.weights();
+        P.thr = thr;
+        c->vcur ^= 1;
+        c->k += 1;
+        return P;
+    };
+    for (int it = 0; it < n; ++it)
+        for (int sw = 0; sw < c->sweeps; ++sw) {
+            sgtv::SmallSplit P{};
+            const bool with_split = it > 0 && sw == 0;
+            if (with_split) P = split();
+            const float *x = S.vt == SGTV_F32 ? c->f[c->fcur].as<float>() : c->fs.as<float>();
+            HIP_TRY(sgtv::launch_small_forward(S.rows(), S.vt, S.row_of.as<int32_t>(), x, c->y.as<float>(),
+                                               c->r.as<float>(), c->ratio.as<float>(), with_split ? &P : nullptr,
+                                               c->grouping, c->stream));
+            sgtv::SmallUpdate U{};
+            U.g = c->f[c->fcur].as<float>();
+            U.g_next = c->f[c->fcur ^ 1].as<float>();
+            U.gs_next = S.vt == SGTV_F32 ? nullptr : c->fs.as<float>();
+            U.v = c->v[c->vcur].as<float>();
+            U.a = c->a[c->vcur].as<float>();
+            U.sens = S.sens.as<float>();
+            U.H = S.H.as<float>();
+            U.htab = S.htab.as<float>();
+            U.grid = S.grid;
+            U.wts = S.weights();
+            U.lam = static_cast<float>(c->rho);
+            HIP_TRY(sgtv::launch_small_back(S.cols(), S.vt, c->ratio.as<float>(), U, c->grouping, c->stream));
+            c->fcur ^= 1;
+        }
+    if (n > 0) {
+        const sgtv::SmallSplit P = split();
+        HIP_TRY(sgtv::launch_split_update(P.f, P.v_old, P.a_old, P.v_new, P.a_new, P.grid, P.wts, c->grouping, thr,
+                                          c->stream));
+    }
     return SGTV_OK;
 }
 
@@ -2356,6 +2527,14 @@ int sgtv_load_system(sgtv_ctx ctx, const char *path) {
                            (t.idx24 != sgtv::kIdxStream ||
                             rec_of(T->poff).bytes == 4 * (t.n_rb * t.ns * t.waves + 1 + 32 * n_lists));
             }
+        if (S.small()) {   // the second copy of a small scan: lines of rows (permuted) and columns
+            const int64_t nr = (S.I + 63) / 64, nc = (S.J + 63) / 64;
+            const int64_t vb = S.vt == SGTV_F32 ? 4 : 2;
+            sizes_ok = sizes_ok && S.n_rslices == nr && S.n_cslices == nc && rec_of(S.rs_ptr).bytes == 8 * (nr + 1) &&
+                       rec_of(S.cs_ptr).bytes == 8 * (nc + 1) && rec_of(S.rs_val).bytes == rec_of(S.rs_idx).bytes / 4 * vb &&
+                       rec_of(S.cs_val).bytes == rec_of(S.cs_idx).bytes / 4 * vb;
+            for (const int64_t r : S.perm) sizes_ok = sizes_ok && r >= 0 && r < S.I;
+        }
         if (!sizes_ok) return fail(SGTV_EINVAL, std::string(path) + ": inconsistent arrays");
         for (size_t a = 0; a < bufs.size(); ++a)
             if (rec[a].present) HIP_TRY(bufs[a]->alloc(static_cast<size_t>(rec[a].bytes)));
@@ -2369,6 +2548,8 @@ int sgtv_load_system(sgtv_ctx ctx, const char *path) {
             HIP_TRY(S.fpart.alloc(static_cast<size_t>(m.fpart_bytes)));
             HIP_TRY(S.bpart.alloc(static_cast<size_t>(m.bpart_bytes)));
             if (int e = alloc_counters(ctx, S)) return e;
+            if (S.small())
+                if (int e = upload_row_of(S)) return e;
         }
         if (int e = compute_sensitivity(ctx, S, nullptr)) return e;
         install_system(ctx, std::move(Sp));
@@ -2555,7 +2736,7 @@ int context_graph(sgtv_ctx ctx, int n_iters, Context::Graph *out) {
     ctx->stream = ctx->cap;
     hipError_t e = hipStreamBeginCapture(ctx->cap, hipStreamCaptureModeRelaxed);
     int status = e == hipSuccess ? SGTV_OK : hip_fail(e, "hipStreamBeginCapture");
-    for (int it = 0; it < n_iters && status == SGTV_OK && e == hipSuccess; ++it) status = step(ctx);
+    if (status == SGTV_OK) status = steps(ctx, n_iters);
     hipGraph_t graph = nullptr;
     if (e == hipSuccess) {
         hipError_t e2 = hipStreamEndCapture(ctx->cap, &graph);
@@ -2604,11 +2785,7 @@ int sgtv_iterate(sgtv_ctx ctx, int n_iters) {
     if (int e = check_ready(ctx)) return e;
     if (n_iters < 0) return fail(SGTV_EINVAL, "n_iters must be >= 0");
     DeviceGuard g(ctx->device);
-    if (!ctx->use_graphs || ctx->profiling || n_iters < 2) {
-        for (int it = 0; it < n_iters; ++it)
-            if (int e = step(ctx)) return e;
-        return SGTV_OK;
-    }
+    if (!ctx->use_graphs || ctx->profiling || n_iters < 2) return steps(ctx, n_iters);
     Context::Graph gr[2];
     int times[2];
     if (int e = context_graphs(ctx, n_iters, gr, times)) return e;
@@ -2850,7 +3027,8 @@ int64_t sgtv_workspace_bytes(int64_t I, int64_t J, int64_t nnz, int storage_dtyp
         return stored * (idx_bytes + vb) + lists * 8.0 + order;
     };
     int64_t ns_f = 1, ns_b = 1;
-    const double matrix = copy_bytes(I, J, &ns_f) + copy_bytes(J, I, &ns_b);
+    double matrix = copy_bytes(I, J, &ns_f) + copy_bytes(J, I, &ns_b);
+    if (nnz < kSmallScan) matrix += 2.3 * static_cast<double>(nnz) * (4.0 + vb) + 4.0 * I;   // small_scan
     const int64_t vectors = 4 * (3 * J + 2 * 4 * J + 2 * J + 2 * J)   // f x2, fs, v x2, a x2, sens, H
                             + 4 * 3 * I                                   // y, r, ratio
                             + 4 * (ns_f * I + ns_b * J)                   // partial sums
@@ -2872,7 +3050,7 @@ int sgtv_device_bytes(sgtv_ctx ctx, int64_t *bytes) {
         for (const DBuf *d : {&S.rs_ptr, &S.rs_idx, &S.rs_val, &S.cs_ptr, &S.cs_idx, &S.cs_val, &S.colscale,
                               &S.sens, &S.H, &S.htab, &S.wbuf, &S.fpart, &S.bpart, &S.fwd.pk, &S.fwd.val,
                               &S.fwd.goff, &S.fwd.poff, &S.fwd.slot, &S.back.pk, &S.back.val, &S.back.goff,
-                              &S.back.poff, &S.back.slot, &S.fcount, &S.bcount})
+                              &S.back.poff, &S.back.slot, &S.fcount, &S.bcount, &S.row_of})
             add(d);
     }
     *bytes = b;
@@ -3316,6 +3494,7 @@ int sgtv_batch_add_scan(sgtv_batch b, int64_t I, int32_t ny, int32_t nx, int32_t
     sgtv_ctx c = nullptr;
     if (int e = sgtv_create(&c, b->device, b->stream)) return e;
     std::unique_ptr<sgtv_ctx_s> own(c);
+    c->in_batch = true;
     sgtv_schedule sch{};
     if (schedule) sch = *schedule;
     sch.format = SGTV_FORMAT_TILED;

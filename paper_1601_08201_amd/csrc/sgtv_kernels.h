@@ -255,6 +255,31 @@ hipError_t launch_split_from_state(const float *v, const float *a, float *d, flo
                                    const Grid &grid, int grouping, hipStream_t st);
 hipError_t launch_div_safe(const float *num, const float *den, float *out, int64_t n,
                            hipStream_t st);
+// Iterations of a small scan (sgtv_kernels.hip): forward product and ratio,
+// beside the split update that P describes (null: none); back product and image
+// update.  row_of: measurement of every line of A.  Indices of A and At carry two
+// marks: the first entry of a slab, and padding.
+constexpr int32_t kSmallCut = INT32_MIN, kSmallPad = int32_t(1) << 30;
+struct SmallSplit {
+    const float *f, *v_old, *a_old;
+    float *v_new, *a_new;
+    Grid grid;
+    Weights wts;
+    float thr;
+    int seg_log2;             // filled by the launcher
+};
+struct SmallUpdate {
+    const float *g;           // image f^k
+    float *g_next, *gs_next;  // new image; its scaled copy for 16-bit values (or nullptr)
+    const float *v, *a, *sens, *H, *htab;
+    Grid grid;
+    Weights wts;
+    float lam;
+};
+hipError_t launch_small_forward(const Sell &A, int vt, const int32_t *row_of, const float *x, const float *y,
+                                const float *r, float *ratio, const SmallSplit *P, int grouping, hipStream_t st);
+hipError_t launch_small_back(const Sell &At, int vt, const float *ratio, const SmallUpdate &U, int grouping,
+                             hipStream_t st);
 // first[0], first[1] (all ones before): smallest index of a y that is negative
 // or not finite, of an r that is not finite and positive
 hipError_t launch_check_data(const float *y, const float *r, int64_t n, uint32_t *first, hipStream_t st);
