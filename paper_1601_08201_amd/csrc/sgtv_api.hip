@@ -1932,20 +1932,22 @@ int step(sgtv_ctx_s *c) {
     return SGTV_OK;
 }
 
-// n ADMM iterations as a launch sequence on the context stream.  On a small
-// scan's second copy the split update of an iteration shares a launch with the
-// next forward product; the last one has its own.  Kernel timing, the fused update
-// and the row-block epilogues keep to the tiles.
+// n ADMM iterations as a launch sequence on the context stream.  The split update
+// of an iteration shares a launch with the next ratio (on a small scan's second
+// copy: with the whole forward product); the last one has its own.  Kernel
+// timing, the fused update, the row-block epilogues and the sliced-ELL format
+// keep their launches apart.
 int steps(sgtv_ctx_s *c, int n) {
     const System &S = *c->sys;
-    if (!S.small() || c->profiling || c->epilogues || c->fused) {
+    if (S.format != SGTV_FORMAT_TILED || c->profiling || c->epilogues || c->fused) {
         for (int it = 0; it < n; ++it)
             if (int e = step(c)) return e;
         return SGTV_OK;
     }
+    const bool small = S.small();
     const float thr = static_cast<float>(c->beta / c->rho);
     auto split = [&]() {
-        sgtv::SmallSplit P{};
+        sgtv::SplitUpdate P{};
         P.f = c->f[c->fcur].as<float>();
         P.v_old = c->v[c->vcur].as<float>();
         P.a_old = c->a[c->vcur].as<float>();
@@ -1960,30 +1962,49 @@ int steps(sgtv_ctx_s *c, int n) {
     };
     for (int it = 0; it < n; ++it)
         for (int sw = 0; sw < c->sweeps; ++sw) {
-            sgtv::SmallSplit P{};
+            sgtv::SplitUpdate P{};
             const bool with_split = it > 0 && sw == 0;
             if (with_split) P = split();
             const float *x = S.vt == SGTV_F32 ? c->f[c->fcur].as<float>() : c->fs.as<float>();
-            HIP_TRY(sgtv::launch_small_forward(S.rows(), S.vt, S.row_of.as<int32_t>(), x, c->y.as<float>(),
-                                               c->r.as<float>(), c->ratio.as<float>(), with_split ? &P : nullptr,
-                                               c->grouping, c->stream));
-            sgtv::SmallUpdate U{};
-            U.g = c->f[c->fcur].as<float>();
-            U.g_next = c->f[c->fcur ^ 1].as<float>();
-            U.gs_next = S.vt == SGTV_F32 ? nullptr : c->fs.as<float>();
-            U.v = c->v[c->vcur].as<float>();
-            U.a = c->a[c->vcur].as<float>();
-            U.sens = S.sens.as<float>();
-            U.H = S.H.as<float>();
-            U.htab = S.htab.as<float>();
-            U.grid = S.grid;
-            U.wts = S.weights();
-            U.lam = static_cast<float>(c->rho);
-            HIP_TRY(sgtv::launch_small_back(S.cols(), S.vt, c->ratio.as<float>(), U, c->grouping, c->stream));
+            if (small) {
+                HIP_TRY(sgtv::launch_small_forward(S.rows(), S.vt, S.row_of.as<int32_t>(), x, c->y.as<float>(),
+                                                   c->r.as<float>(), c->ratio.as<float>(), with_split ? &P : nullptr,
+                                                   c->grouping, c->stream));
+                sgtv::SmallUpdate U{};
+                U.g = c->f[c->fcur].as<float>();
+                U.g_next = c->f[c->fcur ^ 1].as<float>();
+                U.gs_next = S.vt == SGTV_F32 ? nullptr : c->fs.as<float>();
+                U.v = c->v[c->vcur].as<float>();
+                U.a = c->a[c->vcur].as<float>();
+                U.sens = S.sens.as<float>();
+                U.H = S.H.as<float>();
+                U.htab = S.htab.as<float>();
+                U.grid = S.grid;
+                U.wts = S.weights();
+                U.lam = static_cast<float>(c->rho);
+                HIP_TRY(sgtv::launch_small_back(S.cols(), S.vt, c->ratio.as<float>(), U, c->grouping, c->stream));
+            } else {
+                HIP_TRY(sgtv::launch_tiled(S.fwd.map, S.vt, x, S.fpart.as<float>(), c->stream));
+                const sgtv::RatioSums R{S.fpart.as<float>(), S.fwd.map.ns, S.I, c->y.as<float>(), c->r.as<float>(),
+                                        c->ratio.as<float>(), 0};
+                if (with_split)
+                    HIP_TRY(sgtv::launch_ratio_split(R, P, c->grouping, c->stream));
+                else
+                    HIP_TRY(sgtv::launch_ratio_combine(R.part, R.ns, R.n, R.y, R.r, R.ratio, nullptr, false, c->stream,
+                                                       nullptr));
+                HIP_TRY(sgtv::launch_tiled(S.back.map, S.vt, c->ratio.as<float>(), S.bpart.as<float>(), c->stream));
+                HIP_TRY(sgtv::launch_voxel_update(S.bpart.as<float>(), S.back.map.ns,
+                                                  S.vt == SGTV_F32 ? nullptr : S.colscale.as<float>(),
+                                                  c->f[c->fcur].as<float>(), c->f[c->fcur ^ 1].as<float>(),
+                                                  S.vt == SGTV_F32 ? nullptr : c->fs.as<float>(),
+                                                  c->v[c->vcur].as<float>(), c->a[c->vcur].as<float>(),
+                                                  S.sens.as<float>(), S.H.as<float>(), S.htab.as<float>(), S.grid,
+                                                  S.weights(), c->grouping, static_cast<float>(c->rho), c->stream));
+            }
             c->fcur ^= 1;
         }
     if (n > 0) {
-        const sgtv::SmallSplit P = split();
+        const sgtv::SplitUpdate P = split();
         HIP_TRY(sgtv::launch_split_update(P.f, P.v_old, P.a_old, P.v_new, P.a_new, P.grid, P.wts, c->grouping, thr,
                                           c->stream));
     }
@@ -3344,22 +3365,35 @@ int batch_tables(sgtv_batch_s *b) {
     return SGTV_OK;
 }
 
-int batch_step(sgtv_batch_s *b) {
+// n iterations; the split update of an iteration shares a launch with the next
+// ratio, the last one has its own.
+int batch_steps(sgtv_batch_s *b, int n) {
     hipStream_t st = b->stream;
-    HIP_TRY(sgtv::launch_tiled_batch(b->tiles_f.as<sgtv::BatchTile>(), b->n_tiles_f,
-                                     b->maps_f.as<sgtv::TileMap>(), b->xs_f[b->fcur].as<const float *>(),
-                                     b->parts_f.as<float *>(), b->waves, b->lds_f, b->variant, b->storage, st));
-    HIP_TRY(sgtv::launch_ratio_batch(b->rblocks.as<sgtv::BatchBlock>(), b->n_rblocks,
-                                     b->scandev.as<sgtv::ScanDev>(), st));
-    HIP_TRY(sgtv::launch_tiled_batch(b->tiles_b.as<sgtv::BatchTile>(), b->n_tiles_b,
-                                     b->maps_b.as<sgtv::TileMap>(), b->xs_b.as<const float *>(),
-                                     b->parts_b.as<float *>(), b->waves, b->lds_b, b->variant, b->storage, st));
-    HIP_TRY(sgtv::launch_voxel_batch(b->vblocks.as<sgtv::BatchBlock>(), b->n_vblocks,
-                                     b->scandev.as<sgtv::ScanDev>(), b->fcur, b->vcur, st));
-    b->fcur ^= 1;
-    HIP_TRY(sgtv::launch_split_batch(b->sblocks.as<sgtv::BatchBlock>(), b->n_sblocks,
-                                     b->scandev.as<sgtv::ScanDev>(), b->fcur, b->vcur, st));
-    b->vcur ^= 1;
+    for (int it = 0; it < n; ++it) {
+        HIP_TRY(sgtv::launch_tiled_batch(b->tiles_f.as<sgtv::BatchTile>(), b->n_tiles_f,
+                                         b->maps_f.as<sgtv::TileMap>(), b->xs_f[b->fcur].as<const float *>(),
+                                         b->parts_f.as<float *>(), b->waves, b->lds_f, b->variant, b->storage, st));
+        if (it == 0) {
+            HIP_TRY(sgtv::launch_ratio_batch(b->rblocks.as<sgtv::BatchBlock>(), b->n_rblocks,
+                                             b->scandev.as<sgtv::ScanDev>(), st));
+        } else {
+            HIP_TRY(sgtv::launch_ratio_split_batch(b->rblocks.as<sgtv::BatchBlock>(), b->n_rblocks,
+                                                   b->sblocks.as<sgtv::BatchBlock>(), b->n_sblocks,
+                                                   b->scandev.as<sgtv::ScanDev>(), b->fcur, b->vcur, st));
+            b->vcur ^= 1;
+        }
+        HIP_TRY(sgtv::launch_tiled_batch(b->tiles_b.as<sgtv::BatchTile>(), b->n_tiles_b,
+                                         b->maps_b.as<sgtv::TileMap>(), b->xs_b.as<const float *>(),
+                                         b->parts_b.as<float *>(), b->waves, b->lds_b, b->variant, b->storage, st));
+        HIP_TRY(sgtv::launch_voxel_batch(b->vblocks.as<sgtv::BatchBlock>(), b->n_vblocks,
+                                         b->scandev.as<sgtv::ScanDev>(), b->fcur, b->vcur, st));
+        b->fcur ^= 1;
+    }
+    if (n > 0) {
+        HIP_TRY(sgtv::launch_split_batch(b->sblocks.as<sgtv::BatchBlock>(), b->n_sblocks,
+                                         b->scandev.as<sgtv::ScanDev>(), b->fcur, b->vcur, st));
+        b->vcur ^= 1;
+    }
     return SGTV_OK;
 }
 
@@ -3584,7 +3618,7 @@ int batch_graph(sgtv_batch b, int n_iters, sgtv_ctx_s::Graph *out) {
     b->stream = b->cap;
     hipError_t e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeRelaxed);
     int status = e == hipSuccess ? SGTV_OK : hip_fail(e, "hipStreamBeginCapture");
-    for (int it = 0; it < n_iters && status == SGTV_OK && e == hipSuccess; ++it) status = batch_step(b);
+    if (status == SGTV_OK) status = batch_steps(b, n_iters);
     hipGraph_t graph = nullptr;
     if (e == hipSuccess) {
         hipError_t e2 = hipStreamEndCapture(b->cap, &graph);

@@ -71,11 +71,11 @@ __device__ __forceinline__ void block_sum_store(double v, double *out) {
 // twenty times longer, run faster in dispatch order.
 constexpr unsigned kXcds = 8;
 
-__device__ __forceinline__ unsigned xcd_block() {
-    const unsigned n = gridDim.x, b = blockIdx.x;
+__device__ __forceinline__ unsigned xcd_block(unsigned n, unsigned b) {
     const unsigned x = b % kXcds, k = b / kXcds, q = n / kXcds, r = n % kXcds;
     return x * q + (x < r ? x : r) + k;
 }
+__device__ __forceinline__ unsigned xcd_block() { return xcd_block(gridDim.x, blockIdx.x); }
 
 // ---------------------------------------------------------------- geometry
 __device__ __forceinline__ int64_t neighbour(const Grid &g, int64_t s, int iy, int ix, int p) {
@@ -264,6 +264,29 @@ __device__ __forceinline__ void batch_ratio_elem(const ScanDev &S, int64_t i) {
     for (int k = 1; k < S.ns_f; ++k) acc += S.fpart[static_cast<int64_t>(k) * S.I + i];
     const float p = acc + S.r[i];
     S.ratio[i] = S.y[i] / p;
+}
+
+// ratio_i = y_i / (sum_k part[k][i] + r_i), four rows at position i of n4
+typedef float ratio4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void ratio4_at(int64_t i, const float *part, int ns, int64_t n4, const float *y,
+                                          const float *r, float *ratio) {
+    const ratio4 *p4 = reinterpret_cast<const ratio4 *>(part);
+    const ratio4 ri = reinterpret_cast<const ratio4 *>(r)[i];
+    const ratio4 yi = reinterpret_cast<const ratio4 *>(y)[i];
+    ratio4 acc = p4[i];
+    for (int k = 1; k < ns; ++k) {
+        const ratio4 t = p4[static_cast<int64_t>(k) * n4 + i];
+        acc.x += t.x;
+        acc.y += t.y;
+        acc.z += t.z;
+        acc.w += t.w;
+    }
+    ratio4 q;
+    q.x = yi.x / (acc.x + ri.x);
+    q.y = yi.y / (acc.y + ri.y);
+    q.z = yi.z / (acc.z + ri.z);
+    q.w = yi.w / (acc.w + ri.w);
+    reinterpret_cast<ratio4 *>(ratio)[i] = q;
 }
 
 // image update of hyper-voxel j: reads f[fcur], writes f[fcur ^ 1] (and, for

@@ -187,6 +187,9 @@ hipError_t launch_ratio_batch(const BatchBlock *blocks, int64_t n_blocks, const 
                               hipStream_t st);
 hipError_t launch_voxel_batch(const BatchBlock *blocks, int64_t n_blocks, const ScanDev *scans,
                               int fcur, int vcur, hipStream_t st);
+// ratio beside the split update of the iteration before
+hipError_t launch_ratio_split_batch(const BatchBlock *rblocks, int64_t n_rblocks, const BatchBlock *sblocks,
+                                    int64_t n_sblocks, const ScanDev *scans, int fcur, int vcur, hipStream_t st);
 hipError_t launch_split_batch(const BatchBlock *blocks, int64_t n_blocks, const ScanDev *scans,
                               int fcur, int vcur, hipStream_t st);
 hipError_t launch_tiled(const TileMap &M, int vt, const float *x, float *part, hipStream_t st);
@@ -255,12 +258,8 @@ hipError_t launch_split_from_state(const float *v, const float *a, float *d, flo
                                    const Grid &grid, int grouping, hipStream_t st);
 hipError_t launch_div_safe(const float *num, const float *den, float *out, int64_t n,
                            hipStream_t st);
-// Iterations of a small scan (sgtv_kernels.hip): forward product and ratio,
-// beside the split update that P describes (null: none); back product and image
-// update.  row_of: measurement of every line of A.  Indices of A and At carry two
-// marks: the first entry of a slab, and padding.
-constexpr int32_t kSmallCut = INT32_MIN, kSmallPad = int32_t(1) << 30;
-struct SmallSplit {
+// Split update of an iteration, launched beside work of the next one.
+struct SplitUpdate {
     const float *f, *v_old, *a_old;
     float *v_new, *a_new;
     Grid grid;
@@ -268,6 +267,20 @@ struct SmallSplit {
     float thr;
     int seg_log2;             // filled by the launcher
 };
+struct RatioSums {            // ratio_i = y_i / (sum_k part[k][i] + r_i)
+    const float *part;
+    int ns;
+    int64_t n;
+    const float *y, *r;
+    float *ratio;
+    int vec;                  // filled by the launcher: four rows per thread
+};
+hipError_t launch_ratio_split(RatioSums R, SplitUpdate P, int grouping, hipStream_t st);
+// Iterations of a small scan (sgtv_kernels.hip): forward product and ratio,
+// beside the split update that P describes (null: none); back product and image
+// update.  row_of: measurement of every line of A.  Indices of A and At carry two
+// marks: the first entry of a slab, and padding.
+constexpr int32_t kSmallCut = INT32_MIN, kSmallPad = int32_t(1) << 30;
 struct SmallUpdate {
     const float *g;           // image f^k
     float *g_next, *gs_next;  // new image; its scaled copy for 16-bit values (or nullptr)
@@ -277,7 +290,7 @@ struct SmallUpdate {
     float lam;
 };
 hipError_t launch_small_forward(const Sell &A, int vt, const int32_t *row_of, const float *x, const float *y,
-                                const float *r, float *ratio, const SmallSplit *P, int grouping, hipStream_t st);
+                                const float *r, float *ratio, const SplitUpdate *P, int grouping, hipStream_t st);
 hipError_t launch_small_back(const Sell &At, int vt, const float *ratio, const SmallUpdate &U, int grouping,
                              hipStream_t st);
 // first[0], first[1] (all ones before): smallest index of a y that is negative

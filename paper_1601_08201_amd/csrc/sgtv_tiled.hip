@@ -777,26 +777,9 @@ __global__ __launch_bounds__(kBlock) void k_ratio_combine4(const float *__restri
                                                            const float *__restrict__ r,
                                                            float *__restrict__ ratio) {
     const int64_t n4 = n >> 2;
-    const v4f *p4 = reinterpret_cast<const v4f *>(part);
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n4;
-         i += static_cast<int64_t>(gridDim.x) * kBlock) {
-        const v4f ri = reinterpret_cast<const v4f *>(r)[i];
-        const v4f yi = reinterpret_cast<const v4f *>(y)[i];
-        v4f acc = p4[i];
-        for (int k = 1; k < ns; ++k) {
-            const v4f t = p4[static_cast<int64_t>(k) * n4 + i];
-            acc.x += t.x;
-            acc.y += t.y;
-            acc.z += t.z;
-            acc.w += t.w;
-        }
-        v4f q;
-        q.x = yi.x / (acc.x + ri.x);
-        q.y = yi.y / (acc.y + ri.y);
-        q.z = yi.z / (acc.z + ri.z);
-        q.w = yi.w / (acc.w + ri.w);
-        reinterpret_cast<v4f *>(ratio)[i] = q;
-    }
+         i += static_cast<int64_t>(gridDim.x) * kBlock)
+        ratio4_at(i, part, ns, n4, y, r, ratio);
 }
 
 // ratio_i = y_i / (sum_k part[k][i] + r_i), with optional FP64 partials of
