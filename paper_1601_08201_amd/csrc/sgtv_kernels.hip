@@ -238,7 +238,7 @@ __global__ __launch_bounds__(kBlock) void k_split_update(
 // only the image and the forward sums, each alone is a launch that ends before
 // the memory is busy.  Blocks [0, n_split): split update, then the ratio.
 // us an iteration, apart / together: 64 x 64 x 64 48.7 / 47.1, 128 x 128 x 128
-// with 32 entries per column 337 / 333.
+// with 64 entries per column 337 / 333.
 template <int GROUPING, bool WFULL>
 __global__ __launch_bounds__(kBlock) void k_ratio_split(RatioSums R, SplitUpdate P, unsigned n_split) {
     if (blockIdx.x < n_split) {
