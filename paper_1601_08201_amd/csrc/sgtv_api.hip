@@ -1,6 +1,6 @@
 // C ABI of the spectrally grouped TV reconstruction library (declared in
-// include/sgtv.h): argument validation, the two sliced-ELL copies of the
-// system matrix, device buffers of the ADMM state and the per-iteration
+// include/sgtv.h): argument validation, the copies of the system matrix
+// (tiled and sliced ELL), device buffers of the ADMM state and the per-iteration
 // launch sequence.
 #include <hip/hip_runtime.h>
 #include <fcntl.h>
@@ -206,7 +206,7 @@ void on_threads(int64_t n_items, Fn work);
 template <class V>
 void pack_sell(int64_t n_lines, const std::vector<int64_t> &lptr, const std::vector<int32_t> &lidx,
                const std::vector<V> &lval, std::vector<int64_t> &sptr, std::vector<int32_t> &idx,
-               std::vector<V> &val, int32_t fill = 0) {
+               std::vector<V> &val) {
     const int64_t n_slices = (n_lines + sgtv::kSliceRows - 1) / sgtv::kSliceRows;
     sptr.assign(static_cast<size_t>(n_slices + 1), 0);
     for (int64_t k = 0; k < n_slices; ++k) {
@@ -216,7 +216,7 @@ void pack_sell(int64_t n_lines, const std::vector<int64_t> &lptr, const std::vec
         width = (width + 3) / 4 * 4;
         sptr[k + 1] = sptr[k] + width * 64;
     }
-    idx.assign(static_cast<size_t>(sptr[n_slices]), fill);
+    idx.assign(static_cast<size_t>(sptr[n_slices]), 0);
     val.assign(static_cast<size_t>(sptr[n_slices]), V(0));
     on_threads(n_slices, [&](int64_t first, int64_t step) {
         for (int64_t k = first; k < n_slices; k += step)
@@ -1413,42 +1413,42 @@ template <class V>
 bool pack_small_side(const sgtv::TileMap &M, const std::vector<int64_t> &lptr, const std::vector<int32_t> &lidx,
                      const std::vector<V> &lval, const std::vector<int64_t> &lines, std::vector<int64_t> &sptr,
                      std::vector<int32_t> &idx, std::vector<V> &val) {
-    const int64_t n = static_cast<int64_t>(lines.size());
-    std::vector<int64_t> ptr(static_cast<size_t>(n + 1), 0);
-    for (int64_t k = 0; k < n; ++k) {
-        const int64_t len = lptr[lines[k] + 1] - lptr[lines[k]];
-        if (len > kSmallLine) return false;
-        ptr[k + 1] = ptr[k] + len;
+    const int64_t n = static_cast<int64_t>(lines.size()), n_slices = (n + 63) / 64;
+    auto len_of = [&](int64_t k) { return lptr[lines[k] + 1] - lptr[lines[k]]; };
+    sptr.assign(static_cast<size_t>(n_slices + 1), 0);
+    for (int64_t sl = 0; sl < n_slices; ++sl) {
+        int64_t width = 0;
+        for (int64_t k = sl * 64; k < std::min(n, (sl + 1) * 64); ++k) width = std::max(width, len_of(k));
+        if (width > kSmallLine) return false;
+        sptr[sl + 1] = sptr[sl] + (width + 3) / 4 * 4 * 64;
     }
-    std::vector<int32_t> ii(lidx.size());
-    std::vector<V> vv(lval.size());
-    constexpr int64_t kPiece = 1024;
-    on_threads((n + kPiece - 1) / kPiece, [&](int64_t first, int64_t step) {
+    idx.assign(static_cast<size_t>(sptr[n_slices]), sgtv::kSmallPad);
+    val.assign(static_cast<size_t>(sptr[n_slices]), V(0));
+    on_threads(n_slices, [&](int64_t first, int64_t step) {
         std::vector<int64_t> order;
-        for (int64_t piece = first; piece * kPiece < n; piece += step)
-            for (int64_t k = piece * kPiece; k < std::min(n, (piece + 1) * kPiece); ++k) {
-                const int64_t b = lptr[lines[k]], len = ptr[k + 1] - ptr[k];
-                order.resize(static_cast<size_t>(len));
-                bool sorted = true;
-                for (int64_t t = 0; t < len; ++t) {
-                    order[t] = b + t;
-                    sorted = sorted && (t == 0 || lidx[b + t - 1] / M.cb <= lidx[b + t] / M.cb);
-                }
-                if (!sorted)
+        for (int64_t sl = first; sl < n_slices; sl += step)
+            for (int64_t k = sl * 64; k < std::min(n, (sl + 1) * 64); ++k) {
+                const int64_t from = lptr[lines[k]], len = len_of(k);
+                const bool ascending = std::is_sorted(lidx.begin() + from, lidx.begin() + from + len);
+                if (!ascending) {
+                    order.resize(static_cast<size_t>(len));
+                    for (int64_t t = 0; t < len; ++t) order[t] = from + t;
                     std::stable_sort(order.begin(), order.end(),
                                      [&](int64_t x, int64_t y) { return lidx[x] / M.cb < lidx[y] / M.cb; });
+                }
                 int slab = 0;
                 for (int64_t t = 0; t < len; ++t) {
-                    const int32_t col = lidx[order[t]];
+                    const int64_t src = ascending ? from + t : order[t];
+                    const int32_t col = lidx[src];
                     const int was = slab;
-                    while (col / M.cb >= M.slab_begin[slab + 1]) ++slab;
+                    while (col >= static_cast<int64_t>(M.slab_begin[slab + 1]) * M.cb) ++slab;
                     const bool cut = t > 0 && slab != was;
-                    ii[ptr[k] + t] = cut ? col | sgtv::kSmallCut : col;
-                    vv[ptr[k] + t] = lval[order[t]];
+                    const int64_t pos = sptr[sl] + (t / 4) * 256 + (k - sl * 64) * 4 + t % 4;
+                    idx[pos] = cut ? col | sgtv::kSmallCut : col;
+                    val[pos] = lval[src];
                 }
             }
     });
-    pack_sell(n, ptr, ii, vv, sptr, idx, val, sgtv::kSmallPad);
     return true;
 }
 
