@@ -119,3 +119,29 @@ def test_small_scan_from_a_file_and_a_workspace(sg, tmp_path):
     np.testing.assert_array_equal(images[0], images[1])
     np.testing.assert_array_equal(images[0], images[2])
     assert C.device_bytes() == 0
+
+
+@pytest.mark.parametrize("I,ny,nx,Q,weights,grouping,sweeps,storage", [
+    (4096, 16, 16, 32, None, 0, 1, "f32"),    # four rows of the ratio per thread
+    (4097, 9, 41, 54, 4, 0, 2, "f32"),        # one row per thread
+    (3002, 5, 7, 129, "full", 1, 1, "bf16"),  # more spectral bins than a segment has lanes
+    (30001, 1, 3, 1, None, 0, 3, "f32"),      # fewer bins than a block of the split update
+])
+def test_split_beside_ratio_equals_apart(sg, I, ny, nx, Q, weights, grouping, sweeps, storage):
+    """With kernel timing on, every step of an iteration has its own launch."""
+    J = ny * nx * Q
+    rowptr, col, val = csr(I, J, 6, 2, "even")
+    rng = np.random.default_rng(5)
+    w = None if weights is None else (rng.random(4 if weights == 4 else 4 * J) + 0.3).astype(np.float32)
+    y, r = rng.poisson(6.0, I).astype(np.float32), np.full(I, 0.1, np.float32)
+    A, B = sg.Reconstructor(), sg.Reconstructor()
+    for R in (A, B):
+        R.set_schedule(variant=1).set_system(I, ny, nx, Q, rowptr, col, val, storage=storage, w=w)
+        R.set_grouping(grouping)
+        R.set_data(y, r, 0.2, 1.0, sweeps)
+    B.set_profiling(True)
+    for n in (1, 2, 13):
+        A.iterate(n)
+        B.iterate(n)
+        for a, b in zip(A.state()[:3], B.state()[:3]):
+            np.testing.assert_array_equal(a, b)
