@@ -337,6 +337,9 @@ __global__ __launch_bounds__(kWgradThreads) void k_wgrad(const __bf16 *__restric
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     float bs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int yy = 0; yy < R; ++yy) {
+        // rows outside the image add nothing, whatever dZ and X hold (uniform)
+        const int y = y0 + yy, sy = y + ky - 1;
+        if (y >= H || sy < 0 || sy >= H) continue;
         const unsigned short *drow = ds + yy * kC * kC, *xrow = xs + (yy + ky) * kRowPix * kC;
 #pragma unroll
         for (int p0 = 0; p0 < kC; p0 += 32) {

@@ -347,3 +347,20 @@ def test_device_arrays_in_place(sg):
             got = N.forward(xd, out) if m == "forward" else N.start(xd, m, 1.5, out, 0.1)
             assert np.array_equal(got.cpu().numpy(), hf if m == "forward" else host[m])
     N.close()
+
+
+@pytest.mark.parametrize("B,H", [(1, 16), (48, 20)])
+def test_rows_outside_the_image_add_nothing(sg, B, H):
+    """A non-finite gradient in the first (last) image row does not reach the taps that see that row's
+    neighbour outside the image: their weight gradients keep their bits."""
+    x, t = data(11, B=B, H=H)
+    N = sg.WarmStartNet(layers=1, height=H, max_batch=B).set_params(layer_params(sg, 1, 6))
+    clean, hit = np.empty(sg.wsnet_param_count(1, 64), np.float32), np.empty(sg.wsnet_param_count(1, 64), np.float32)
+    N.backward(x, t, clean)
+    for row, ky in ((0, 0), (H - 1, 2)):
+        bad = t.copy()
+        bad[B // 2, row, 9, 5] = np.inf
+        N.backward(x, bad, hit)
+        w, c = (g[:64 * 9 * 64].reshape(64, 3, 3, 64) for g in (hit, clean))
+        np.testing.assert_array_equal(w[:, ky], c[:, ky])
+        assert not np.isfinite(w[5, 1]).any()   # the taps within the image see it
