@@ -1308,6 +1308,9 @@ int stage_data(sgtv_ctx_s *ctx, const float *y, const float *r, int mk, bool ref
     const System &S = *ctx->sys;
     const size_t n = sizeof(float) * static_cast<size_t>(S.I);
     const float *sy = y, *sr = r;
+    // arrays that the null stream (or a blocking one) is still writing, on a
+    // context stream that does not wait for it
+    if (mk == SGTV_DEVICE) HIP_TRY(hipStreamSynchronize(nullptr));
     if (mk == SGTV_HOST || !refill) {
         float *ty = refill ? ctx->ratio.as<float>() : dy.as<float>();
         float *tr = refill ? S.fpart.as<float>() : dr.as<float>();

@@ -123,3 +123,29 @@ def test_pieces_and_kept_graphs(sg):
         G.set_data(dev[0], dev[1], prob.beta, prob.rho, 1).iterate(n)
         np.testing.assert_array_equal(E.image(), G.image())
         assert E.objective() == G.objective()
+
+
+@pytest.mark.parametrize("case", ["first data", "data again", "sliced ELL"])
+def test_set_data_waits_for_the_default_stream(sg, case):
+    """Device arrays that the default stream is still writing when set_data is called, from a context on a
+    stream of its own: the values that the default stream leaves there are the ones that are used."""
+    import torch
+    prob = datagen.make_problem("small", 6)
+    y, r = torch.from_numpy(prob.y).cuda(), torch.from_numpy(prob.r).cuda()
+    side = torch.cuda.Stream()
+    R, E = sg.Reconstructor(stream=side.cuda_stream), sg.Reconstructor()
+    for X in (R, E):
+        if case == "sliced ELL":
+            X.set_schedule(format=1)
+        X.set_system(prob.I, prob.ny, prob.nx, prob.Q, prob.rowptr, prob.col, prob.val)
+    if case == "data again":
+        R.set_data(torch.ones_like(y), r, prob.beta, prob.rho, 1).iterate(3)
+    late = torch.zeros_like(y)
+    a = torch.rand((8192, 8192), device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(8):               # some milliseconds of work before y is there
+        a = (a @ a) * 1e-4
+    late.copy_(y)
+    R.set_data(late, r, prob.beta, prob.rho, 1).iterate(4)
+    E.set_data(y, r, prob.beta, prob.rho, 1).iterate(4)
+    np.testing.assert_array_equal(R.image(), E.image())
