@@ -1276,6 +1276,18 @@ int check_mem_kind(int mk) {
 hipMemcpyKind to_caller(int mk) { return mk == SGTV_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice; }
 hipMemcpyKind from_caller(int mk) { return mk == SGTV_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice; }
 
+// Memory that kernels of a device may use where it lies.  Another GPU's memory is
+// copied (the copies work across GPUs, kernel accesses only between peers), like
+// everything that is not known.
+bool lies_on(const hipPointerAttribute_t &a, int device) { return a.type == hipMemoryTypeDevice && a.device == device; }
+
+bool in_place(const void *p, int device) {
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) == hipSuccess) return lies_on(a, device);
+    (void)hipGetLastError();
+    return false;
+}
+
 // Upload a validated float array of n values from caller memory into dst.
 int stage_floats(DBuf &dst, const float *src, int64_t n, int mk, hipStream_t st,
                  bool (*ok)(float), const char *what) {
@@ -1300,9 +1312,9 @@ int data_error(int64_t iy, int64_t ir) {
 }
 
 // Checks y and r on the device and puts them into dy and dr (fresh buffers, or,
-// with refill, the context's own, untouched when a value is refused: host arrays
-// then pass through the ratio and the partial sums, which hold nothing between
-// calls).  Checking 1 M measurements on the host took 3 ms a call with the
+// with refill, the context's own, untouched when a value is refused: arrays that
+// are not on the context's GPU then pass through the ratio and the partial sums,
+// which hold nothing between calls).  Checking 1 M measurements on the host took 3 ms a call with the
 // copies, this 0.4 ms.
 int stage_data(sgtv_ctx_s *ctx, const float *y, const float *r, int mk, bool refill, DBuf &dy, DBuf &dr) {
     const System &S = *ctx->sys;
@@ -1311,7 +1323,8 @@ int stage_data(sgtv_ctx_s *ctx, const float *y, const float *r, int mk, bool ref
     // arrays that the null stream (or a blocking one) is still writing, on a
     // context stream that does not wait for it
     if (mk == SGTV_DEVICE) HIP_TRY(hipStreamSynchronize(nullptr));
-    if (mk == SGTV_HOST || !refill) {
+    const bool direct = refill && mk == SGTV_DEVICE && in_place(y, ctx->device) && in_place(r, ctx->device);
+    if (!direct) {
         float *ty = refill ? ctx->ratio.as<float>() : dy.as<float>();
         float *tr = refill ? S.fpart.as<float>() : dr.as<float>();
         HIP_TRY(hipMemcpyAsync(ty, y, n, from_caller(mk), ctx->stream));
@@ -3790,12 +3803,12 @@ int net_weights(wsnet_s *n) {
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// Caller data as 16-byte aligned device memory: device arrays are read in place
-// by calls that wait for the device before they return, everything else is
-// copied to dst (a call that does not wait leaves the caller's array alone as
+// Caller data as 16-byte aligned device memory: arrays on the network's GPU are
+// read in place by calls that wait for the device before they return, everything
+// else is copied to dst (a call that does not wait leaves the caller's array alone as
 // soon as the copy is done).
 int net_stage(wsnet_s *n, DBuf &dst, const float *src, int64_t count, int mk, bool waits, const float **p) {
-    if (waits && mk == SGTV_DEVICE && aligned16(src)) {
+    if (waits && mk == SGTV_DEVICE && aligned16(src) && in_place(src, n->device)) {
         *p = src;
         return SGTV_OK;
     }
@@ -3980,7 +3993,7 @@ int wsnet_forward(wsnet net, const float *x_in, int32_t batch, float *x0, int me
     const float *x = nullptr;
     if (int e = net_stage(net, net->xin, x_in, cnt, mem_kind, true, &x)) return e;
     // the input has been read by the time the last layer writes: x0 may overlap it
-    float *out = mem_kind == SGTV_DEVICE && aligned16(x0) ? x0 : net->out.as<float>();
+    float *out = mem_kind == SGTV_DEVICE && aligned16(x0) && in_place(x0, net->device) ? x0 : net->out.as<float>();
     HIP_TRY(sgtv::wsn::to_bf16(x, bf(net->acts), cnt, net->stream));
     if (int e = net_layers(net, batch, nullptr, out)) return e;
     if (out != x0) HIP_TRY(hipMemcpyAsync(x0, out, sizeof(float) * cnt, to_caller(mem_kind), net->stream));
@@ -4006,7 +4019,8 @@ int wsnet_start(wsnet net, const float *f, int32_t batch, int mode, double c_out
     // f is read again beside x0's writes, value by value: x0 is written in place
     // where it is f or apart from it
     const bool apart = x0 + cnt <= x || x + cnt <= x0;
-    float *out = mem_kind == SGTV_DEVICE && aligned16(x0) && (x0 == x || apart) ? x0 : net->tgt.as<float>();
+    const bool written = mem_kind == SGTV_DEVICE && aligned16(x0) && (x0 == x || apart) && in_place(x0, net->device);
+    float *out = written ? x0 : net->tgt.as<float>();
     HIP_TRY(sgtv::wsn::start_image(x, net->out.as<float>(), net->isum.as<double>(), net->img, batch,
                                    static_cast<float>(c_out), mode == WSNET_START_RATIO, static_cast<float>(floor), out,
                                    net->stream));
