@@ -1068,8 +1068,13 @@ int pack_tiled(PackedTiled &T, int64_t n_rows, int64_t n_cols, const std::vector
     plan_lists(n_rows, n_cols, rp, ci, t, stream || idx24, P);
     if (stream)
         if (int e = stream_lists(P, ci, vals, T.pk, pv, T.goff, T.poff, T.map)) return e;
-    if (T.pk.empty())
+    if (T.pk.empty()) {
+        if (stream && !idx24) {   // 32-bit lists hold the rows in their own order
+            P = TileLists{};
+            plan_lists(n_rows, n_cols, rp, ci, t, false, P);
+        }
         if (int e = place_lists(P, rp, ci, vals, idx24, T.pk, pv, T.goff, T.poff, T.map)) return e;
+    }
     T.slot.swap(P.slot_of);
     if constexpr (sizeof(V) == 4) T.v32.swap(pv);
     else T.v16.swap(pv);

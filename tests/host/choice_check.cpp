@@ -1,13 +1,47 @@
 // Host-only checks of the choices that the library makes before it launches
 // anything (this file includes the library source; no GPU is touched):
 //   * arrays are used in place only where they are device memory of the GPU that
-//     reads them.
+//     reads them;
+//   * a tiled copy that ends in 32-bit lists (too sparse to stream, too tall for
+//     24 bits) gives the row sums, walked as the kernel does.
 // Prints one line per case and "ok" at the end; exits 1 after a failure.
 #include "../../paper_1601_08201_amd/csrc/sgtv_api.hip"
 
 #include <cstdio>
+#include <set>
 
 namespace {
+
+struct Csr {
+    int64_t n_rows = 0, n_cols = 0;
+    std::vector<int64_t> rp;
+    std::vector<int32_t> ci;
+    std::vector<float> v;
+};
+
+uint64_t lcg(uint64_t &s) {
+    s = s * 6364136223846793005ull + 1442695040888963407ull;
+    return s >> 33;
+}
+
+// len(r) entries in row r, in uniform columns
+template <class Len>
+Csr make_csr(int64_t n_rows, int64_t n_cols, uint64_t seed, Len len) {
+    Csr m;
+    m.n_rows = n_rows;
+    m.n_cols = n_cols;
+    m.rp.push_back(0);
+    uint64_t s = seed;
+    for (int64_t r = 0; r < n_rows; ++r) {
+        for (int64_t e = len(r); e > 0; --e) {
+            m.ci.push_back(static_cast<int32_t>(lcg(s) % n_cols));
+            m.v.push_back(static_cast<float>(lcg(s) % 1000 + 1) / 997.0f);
+        }
+        std::sort(m.ci.begin() + m.rp.back(), m.ci.end());
+        m.rp.push_back(static_cast<int64_t>(m.ci.size()));
+    }
+    return m;
+}
 
 int failures = 0;
 
@@ -35,10 +69,58 @@ void check_memory() {
     std::printf("memory in place\n");
 }
 
+// The 32-bit lists of a copy as tiled_body walks them: groups of 64 lanes (four
+// groups a batch, the rest one by one), row sums read through the slot table.
+void check_lists32(const char *name, const Csr &m, TileParams t) {
+    PackedTiled T;
+    CHECK(pack_tiled(T, m.n_rows, m.n_cols, m.rp, m.ci, m.v, t, true) == SGTV_OK, "%s: packing failed", name);
+    const sgtv::TileMap &M = T.map;
+    CHECK(M.idx24 == 0, "%s: format %d", name, M.idx24);
+    const int64_t RB = static_cast<int64_t>(M.waves) * M.rw;
+    std::vector<double> ref(static_cast<size_t>(m.n_rows * M.ns), 0.0), got(ref.size(), 0.0);
+    std::vector<int> slab_of;
+    for (int k = 0; k < M.ns; ++k) slab_of.insert(slab_of.end(), M.slab_begin[k + 1] - M.slab_begin[k], k);
+    for (int64_t r = 0; r < m.n_rows; ++r)
+        for (int64_t k = m.rp[r]; k < m.rp[r + 1]; ++k)
+            ref[slab_of[m.ci[k] / M.cb] * m.n_rows + r] += m.v[k] * static_cast<double>(m.ci[k] % 97 + 1);
+    for (int64_t tile = 0; tile < M.n_rb * M.ns; ++tile) {
+        const int64_t rb = tile / M.ns;
+        const int slab = static_cast<int>(tile % M.ns);
+        std::vector<double> acc(static_cast<size_t>(M.waves) * (M.rw + 1), 0.0);
+        for (int c = M.slab_begin[slab]; c < M.slab_begin[slab + 1]; ++c)
+            for (int w = 0; w < M.waves; ++w) {
+                const int64_t L = (tile * M.cbs_max + (c - M.slab_begin[slab])) * M.waves + w;
+                const int64_t base = static_cast<int64_t>(T.goff[L]) * 64, ng = T.goff[L + 1] - T.goff[L];
+                for (int64_t g = 0; g < ng; ++g) {
+                    std::set<int> rows;
+                    for (int lane = 0; lane < 64; ++lane) {
+                        const int64_t pos = g < ng / 4 * 4 ? base + g / 4 * 256 + lane * 4 + g % 4 : base + g * 64 + lane;
+                        const int row = T.pk[pos] >> 16, col = T.pk[pos] & 0xFFFF;
+                        CHECK(row <= M.rw && (row == M.rw || rows.insert(row).second), "%s: two lanes on a row", name);
+                        if (row < M.rw)
+                            acc[w * (M.rw + 1) + row] +=
+                                T.v32[pos] * static_cast<double>((static_cast<int64_t>(c) * M.cb + col) % 97 + 1);
+                    }
+                }
+            }
+        for (int64_t i = 0; i < RB && rb * RB + i < m.n_rows; ++i) {
+            const int64_t s = T.slot.empty() ? i : T.slot[tile * RB + i];
+            got[slab * m.n_rows + rb * RB + i] = acc[s / M.rw * (M.rw + 1) + s % M.rw];
+        }
+    }
+    for (size_t i = 0; i < ref.size(); ++i)
+        CHECK(std::fabs(got[i] - ref[i]) <= 1e-9 * (1.0 + std::fabs(ref[i])), "%s: row %lld", name,
+              static_cast<long long>(i) % static_cast<long long>(m.n_rows));
+    std::printf("%s: 32-bit lists\n", name);
+}
+
 }  // namespace
 
 int main() {
     check_memory();
+    check_lists32("even rows", make_csr(40000, 250000, 1, [](int64_t) { return 1; }), TileParams{1500, 16, 15000, 2});
+    check_lists32("uneven rows", make_csr(40000, 900000, 2, [](int64_t r) { return 2 + r % 5; }),
+                  TileParams{1500, 16, 15000, 3});
     if (failures) return 1;
     std::printf("ok\n");
     return 0;

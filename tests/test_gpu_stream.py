@@ -88,3 +88,27 @@ def test_streamed_matches_oracle(name, storage):
     err = np.linalg.norm(out[0][0] - f) / np.linalg.norm(f)
     print(name, storage, "rel_l2", err, flush=True)
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_too_sparse_to_stream(storage):
+    """Tiles too tall and wide for 24-bit indices, one entry per voxel: both products read 32-bit lists
+    (tests/test_host_choices.py walks the same shape)."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import oracle
+    from paper_1601_08201_amd import sgtv
+    I, ny, nx, Q = 250000, 20, 20, 100
+    A, y, r = problem(I, ny, nx, Q, 1, 5)
+    rowptr = A.indptr.astype(np.int64)
+    R = sgtv.Reconstructor(device=0)
+    R.set_schedule(fwd_rows_per_wave=1500, fwd_block_cols=15000, fwd_slabs=1, back_rows_per_wave=1500,
+                   back_block_cols=15000, back_slabs=2)
+    R.set_system(I, ny, nx, Q, rowptr, A.indices, A.data, storage=storage).set_data(y, r, 0.1, 1.0)
+    image = R.iterate(3).image()
+    R.close()
+    val = A.data if storage == "f32" else oracle.quantise(A.indices, A.data, ny * nx * Q, storage)[2]
+    p = SimpleNamespace(ny=ny, nx=nx, Q=Q, I=I, J=ny * nx * Q, rowptr=rowptr, col=A.indices, val=val, y=y, r=r,
+                        beta=0.1, rho=1.0, sweeps=1)
+    f = oracle.admm(p, 3, report=False)[0]
+    assert np.linalg.norm(image - f) <= 1e-5 * np.linalg.norm(f)
