@@ -273,13 +273,18 @@ double modelled_us(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_bytes,
 // took 64 us a product, with 256 42 us), the column blocks and slab counts, the
 // fastest by the model above.  Of equally fast ones the first: wide blocks and
 // few slabs.  The rule below stays for heights that are given (a batch's scans
-// fill the GPU together) and other workgroup sizes than the fitted one, and below
-// 2 M entries, where every schedule costs about as much and the model's many
-// slabs cost a batch more (9 x 41 x 54 alone 24.0 against 24.4 us an iteration,
-// 16 such scans in a batch 133 against 58 us): one slab of the gathered vector is
-// at most 2 MiB, so an XCD's 4 MiB L2 keeps it next to the streamed entries.
+// fill the GPU together), for other workgroup sizes and inner loops (simple:
+// false) than the fitted ones, and below 2 M entries, where every schedule costs
+// about as much and the model's many slabs cost a batch more (9 x 41 x 54 alone
+// 24.0 against 24.4 us an iteration, 16 such scans in a batch 133 against 58 us):
+// one slab of the gathered vector is at most 2 MiB, so an XCD's 4 MiB L2 keeps it
+// next to the streamed entries.
+bool modelled(int64_t nnz, int waves, int rw, bool simple) {
+    return rw <= 0 && simple && nnz >= (int64_t(1) << 21) && waves == 16;
+}
+
 TileParams choose_tiles(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_bytes, int waves, int rw, int cb,
-                        int ns) {
+                        int ns, bool simple = true) {
     TileParams t;
     t.waves = waves > 0 ? waves : 16;
     // 16380 = the widest block of the 24-bit index format (a multiple of 4
@@ -301,7 +306,7 @@ TileParams choose_tiles(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_b
     }
     if (t.ns > ncb) t.ns = static_cast<int>(std::max<int64_t>(1, ncb));
     t.rw = rw > 0 ? rw : 64;
-    if (rw > 0 || nnz < (int64_t(1) << 21) || t.waves != 16) {
+    if (!modelled(nnz, t.waves, rw, simple)) {
         if (rw <= 0) {
             // until there is a tile for every CU: more slabs first (up to 8), then
             // shorter tiles (long lists keep the packing dense)
@@ -318,7 +323,7 @@ TileParams choose_tiles(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_b
     }
     TileParams best = t;
     double best_us = 0.0;
-    for (const int widest : {16380, 15976, 12284, 8188, 4092})
+    for (const int widest : {16380, 12284, 8188, 4092})
         for (int k = ns > 0 ? ns : 1; k <= (ns > 0 ? ns : sgtv::kMaxSlabs); ++k) {
             // blocks of even width, as many in every slab
             int64_t nb = std::max<int64_t>(1, (n_cols + widest - 1) / widest);
@@ -329,11 +334,14 @@ TileParams choose_tiles(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_b
             const int slabs = static_cast<int>(std::min<int64_t>(k, blocks));
             // room beside the block, with the spare rows of 32-bit lists
             const int rw_max = std::min<int>(2048, (40960 - cc) / 16 - 1);
+            // slabs too short to stream take tiles that 24-bit indices fit
+            const bool streams = cb > 0 || blocks >= static_cast<int64_t>(sgtv::kStreamBlocks - 1) * slabs + 1;
             for (int rounds = 1; rounds <= 64; ++rounds) {
                 const int64_t n_rb = std::max<int64_t>(1, 256 * rounds / slabs);
                 const int64_t need = (n_rows + 16 * n_rb - 1) / (16 * n_rb);
                 if (need > rw_max) continue;
                 const TileParams q{static_cast<int>(std::max<int64_t>(64, need)), 16, cc, slabs};
+                if (!streams && !sgtv::idx24_fits(q.rw, q.cb)) continue;
                 const double us = modelled_us(n_rows, n_cols, nnz, value_bytes, q);
                 if (best_us == 0.0 || us < 0.99 * best_us) {
                     best = q;
@@ -878,14 +886,21 @@ int place_lists(TileLists &P, const std::vector<int64_t> &rp, const std::vector<
 // that 64 lanes can do with; a step of more than dmax rows inside a lane costs
 // padding entries of dmax rows each.  Leaves the outputs empty and returns
 // SGTV_OK when the format does not pay:
-//   * fewer than kStreamBlocks column blocks a slab: there are no barriers to
+//   * fewer than sgtv::kStreamBlocks column blocks a slab: there are no barriers to
 //     stream across, and 24-bit lists, whose lanes take rows in any order, pack
 //     tighter (64^3 scanner, 2 blocks: 53.6 against 51.2 us an iteration; 16
 //     scans of 9 x 41 x 54, 1 and 2 blocks: 57.4 against 56.2 us);
-//   * more than 1.35 times the groups that dense lists would have.
-constexpr int kStreamBlocks = 3;
+//   * where 24-bit lists would do (narrow: true) more than 1.35 times the groups
+//     that dense lists have, or more than 1.35 times their bytes (base rows and
+//     the ends of streams count: lists with few entries). 96^3 in tiles of 864 x
+//     15800: at 16 entries per column 33.0 against 31.6 us a product, at 8 29.8
+//     against 25.3 us;
+//   * where it is 32-bit lists otherwise, more than twice their bytes. Streams are
+//     the faster ones in every case measured, 128^3 in tiles of 1561 x 15888 with
+//     8, 16 and 24 entries per column 71 / 81 / 91 us a product against 86 / 105 /
+//     115 us, at 1.9, 1.35 and 1.1 times the bytes.
 template <class V>
-int stream_lists(const TileLists &P, const std::vector<int32_t> &ci, const std::vector<V> &vals,
+int stream_lists(const TileLists &P, const std::vector<int32_t> &ci, const std::vector<V> &vals, bool narrow,
                  std::vector<int32_t> &pk, std::vector<V> &pv, std::vector<int32_t> &goff,
                  std::vector<int32_t> &poff, sgtv::TileMap &map) {
     SetupClock clk;
@@ -893,7 +908,7 @@ int stream_lists(const TileLists &P, const std::vector<int32_t> &ci, const std::
     const TileParams &t = P.t;
     const int cbits = sgtv::stream_col_bits(t.cb, t.waves), dmax = (1 << (16 - cbits)) - 1;
     const int64_t n_streams = P.n_rb * t.ns * t.waves;
-    if (P.cbs_max < kStreamBlocks) return SGTV_OK;
+    if (P.cbs_max < sgtv::kStreamBlocks) return SGTV_OK;
     for (int k = 0; k < t.ns; ++k)   // the kernel takes a slab to have a block
         if (P.slab_begin[k] == P.slab_begin[k + 1]) return SGTV_OK;
     struct Run {
@@ -956,7 +971,11 @@ int stream_lists(const TileLists &P, const std::vector<int32_t> &ci, const std::
     }
     for (int64_t L = 0; L < P.n_lists; ++L)
         dense += std::max<int64_t>((P.count[L] + 63) / 64, P.maxrun[L]);
-    if (total * kC * 64 >= (int64_t(1) << 31) || stored * 20 > dense * 27) return SGTV_OK;
+    const double kept = static_cast<double>(total) * kC * 64 * (2 + sizeof(V)) + 132.0 * P.n_lists;
+    const double other = static_cast<double>(dense) * 64 * ((narrow ? 3 : 4) + sizeof(V)) + 8.0 * P.n_lists;
+    if (total * kC * 64 >= (int64_t(1) << 31) || (narrow && stored * 20 > dense * 27) ||
+        kept > (narrow ? 1.35 : 2.0) * other + 65536.0)
+        return SGTV_OK;
     goff.assign(static_cast<size_t>(P.n_lists + 1), 0);
     poff.assign(static_cast<size_t>(n_streams + 1 + P.n_lists * 32), 0);
     pk.assign(static_cast<size_t>((total + 1) * 256), static_cast<int32_t>(t.cb | (t.cb << 16)));
@@ -1067,7 +1086,7 @@ int pack_tiled(PackedTiled &T, int64_t n_rows, int64_t n_cols, const std::vector
     TileLists P;
     plan_lists(n_rows, n_cols, rp, ci, t, stream || idx24, P);
     if (stream)
-        if (int e = stream_lists(P, ci, vals, T.pk, pv, T.goff, T.poff, T.map)) return e;
+        if (int e = stream_lists(P, ci, vals, idx24, T.pk, pv, T.goff, T.poff, T.map)) return e;
     if (T.pk.empty()) {
         if (stream && !idx24) {   // 32-bit lists hold the rows in their own order
             P = TileLists{};
@@ -1605,9 +1624,11 @@ int pack_system(sgtv_ctx_s *c, Packed &PK, int64_t I, int32_t ny, int32_t nx, in
     if (S->format == SGTV_FORMAT_TILED) {
         const sgtv_schedule &q = c->want;
         const int vb = vt == SGTV_F32 ? 4 : 2;
-        const TileParams tf = choose_tiles(I, J, nnz, vb, q.waves, q.fwd_rows_per_wave, q.fwd_block_cols, q.fwd_slabs);
-        const TileParams tb = choose_tiles(J, I, nnz, vb, q.waves, q.back_rows_per_wave, q.back_block_cols, q.back_slabs);
-        const bool var1 = q.variant <= 1;   // the simple loop, the only one on 24-bit indices
+        const bool var1 = q.variant <= 1;   // the simple loop, the only one on streamed and 24-bit lists
+        const TileParams tf = choose_tiles(I, J, nnz, vb, q.waves, q.fwd_rows_per_wave, q.fwd_block_cols, q.fwd_slabs,
+                                           var1);
+        const TileParams tb = choose_tiles(J, I, nnz, vb, q.waves, q.back_rows_per_wave, q.back_block_cols, q.back_slabs,
+                                           var1);
         if (tile_lds_bytes(tf, var1) > 163840 || tile_lds_bytes(tb, var1) > 163840)
             return fail(SGTV_EINVAL, "schedule needs more than 160 KiB of LDS per workgroup");
         S->sched.waves = tf.waves;

@@ -60,6 +60,7 @@ inline bool idx24_fits(int rw, int cb) {
 // covers, else 14 (four float4, up to 16380 columns).
 constexpr int kIdxStream = 2;      // TileMap::idx24 of a streamed copy
 constexpr int kStreamChunk = 8;    // groups per chunk
+constexpr int kStreamBlocks = 3;   // column blocks of a slab from which on lists are streamed
 inline int stream_col_bits(int cb, int waves) { return cb <= 8188 && cb <= 8 * waves * kWave ? 13 : 14; }
 inline bool stream_fits(int rw, int cb, int waves) {
     return rw >= 64 && cb % 4 == 0 && cb <= 16380 && cb <= 16 * waves * kWave;

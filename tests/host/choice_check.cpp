@@ -2,8 +2,9 @@
 // anything (this file includes the library source; no GPU is touched):
 //   * arrays are used in place only where they are device memory of the GPU that
 //     reads them;
-//   * a tiled copy that ends in 32-bit lists (too sparse to stream, too tall for
-//     24 bits) gives the row sums, walked as the kernel does.
+//   * a tiled copy that ends in 32-bit lists (streaming refused, tiles too tall and
+//     wide for 24 bits) gives the row sums, walked as the kernel does;
+//   * the automatic schedule of sparse matrices ends in streamed lists.
 // Prints one line per case and "ok" at the end; exits 1 after a failure.
 #include "../../paper_1601_08201_amd/csrc/sgtv_api.hip"
 
@@ -114,13 +115,46 @@ void check_lists32(const char *name, const Csr &m, TileParams t) {
     std::printf("%s: 32-bit lists\n", name);
 }
 
+// The automatic schedule of a product and the format its copy gets.
+void check_automatic(const char *name, const Csr &m, int want) {
+    const int64_t nnz = m.rp[m.n_rows];
+    const TileParams t = choose_tiles(m.n_rows, m.n_cols, nnz, 4, 0, 0, 0, 0);
+    PackedTiled T;
+    CHECK(pack_tiled(T, m.n_rows, m.n_cols, m.rp, m.ci, m.v, t, true) == SGTV_OK, "%s: packing failed", name);
+    const double bytes = 4.0 * (T.pk.size() + T.v32.size() + T.goff.size() + T.poff.size());
+    std::printf("%s: %d x %d, %d slabs, format %d, %.2f bytes an entry\n", name, t.rw, t.cb, t.ns, T.map.idx24, bytes / nnz);
+    CHECK(want < 0 || T.map.idx24 == want, "%s: format %d", name, T.map.idx24);
+}
+
+void check_rules() {
+    // the pipelined loops read 32-bit lists: the schedule is not the modelled one
+    const TileParams p = choose_tiles(1 << 20, 1 << 21, 1 << 26, 4, 0, 0, 0, 0, false);
+    CHECK(p.rw == 1024 && p.cb == 16380 && p.ns == 4, "pipelined loop: %d x %d, %d", p.rw, p.cb, p.ns);
+    // two column blocks are not streamed: 24-bit lists must fit
+    for (const int64_t rows : {int64_t(3000000), int64_t(5000000), int64_t(9000000)}) {
+        const TileParams t = choose_tiles(rows, 30000, 20 * rows, 4, 0, 0, 0, 0);
+        CHECK(sgtv::idx24_fits(t.rw, t.cb), "30000 columns: %d x %d", t.rw, t.cb);
+    }
+    std::printf("rules of the schedule\n");
+}
+
 }  // namespace
 
 int main() {
     check_memory();
-    check_lists32("even rows", make_csr(40000, 250000, 1, [](int64_t) { return 1; }), TileParams{1500, 16, 15000, 2});
-    check_lists32("uneven rows", make_csr(40000, 900000, 2, [](int64_t r) { return 2 + r % 5; }),
-                  TileParams{1500, 16, 15000, 3});
+    check_rules();
+    const int S = sgtv::kIdxStream;
+    check_automatic("128^3, 4 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 8; }), S);
+    check_automatic("128^3, 8 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 16; }), S);
+    check_automatic("128^3, 8 a voxel, back", make_csr(1 << 21, 1 << 20, 3, [](int64_t) { return 8; }), S);
+    check_automatic("128^3, 16 a voxel", make_csr(1 << 20, 1 << 21, 4, [](int64_t) { return 32; }), S);
+    check_automatic("100 x 100 x 110, 16 a voxel", make_csr(800000, 1100000, 5, [](int64_t) { return 22; }), S);
+    check_automatic("120 x 110 x 90, 20 a voxel, back", make_csr(1188000, 1000000, 6, [](int64_t) { return 20; }), S);
+    check_automatic("128 x 128 x 64, 8 a voxel", make_csr(524288, 1048576, 7, [](int64_t) { return 16; }), S);
+    check_automatic("96^3, 16 a voxel", make_csr(442368, 884736, 8, [](int64_t) { return 32; }), -1);
+    check_lists32("even rows", make_csr(40000, 50000, 1, [](int64_t) { return 3; }), TileParams{1500, 16, 15000, 2});
+    check_lists32("uneven rows", make_csr(60001, 70001, 2, [](int64_t r) { return r % 9 == 4 ? 0 : 1 + r % 70; }),
+                  TileParams{1400, 16, 16000, 3});
     if (failures) return 1;
     std::printf("ok\n");
     return 0;

@@ -91,9 +91,9 @@ def test_streamed_matches_oracle(name, storage):
 
 
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
-def test_too_sparse_to_stream(storage):
-    """Tiles too tall and wide for 24-bit indices, one entry per voxel: both products read 32-bit lists
-    (tests/test_host_choices.py walks the same shape)."""
+def test_slabs_too_short_to_stream(storage):
+    """Slabs of one or two column blocks, tiles too tall and wide for 24-bit indices: both products read 32-bit
+    lists (tests/test_host_choices.py walks such lists)."""
     import torch
     assert torch.cuda.is_available(), "GPU tests need a GPU"
     import oracle
@@ -102,13 +102,40 @@ def test_too_sparse_to_stream(storage):
     A, y, r = problem(I, ny, nx, Q, 1, 5)
     rowptr = A.indptr.astype(np.int64)
     R = sgtv.Reconstructor(device=0)
-    R.set_schedule(fwd_rows_per_wave=1500, fwd_block_cols=15000, fwd_slabs=1, back_rows_per_wave=1500,
-                   back_block_cols=15000, back_slabs=2)
+    R.set_schedule(fwd_rows_per_wave=1500, fwd_block_cols=15000, fwd_slabs=2, back_rows_per_wave=1500,
+                   back_block_cols=15000, back_slabs=9)
     R.set_system(I, ny, nx, Q, rowptr, A.indices, A.data, storage=storage).set_data(y, r, 0.1, 1.0)
     image = R.iterate(3).image()
     R.close()
     val = A.data if storage == "f32" else oracle.quantise(A.indices, A.data, ny * nx * Q, storage)[2]
     p = SimpleNamespace(ny=ny, nx=nx, Q=Q, I=I, J=ny * nx * Q, rowptr=rowptr, col=A.indices, val=val, y=y, r=r,
                         beta=0.1, rho=1.0, sweeps=1)
+    f = oracle.admm(p, 3, report=False)[0]
+    assert np.linalg.norm(image - f) <= 1e-5 * np.linalg.norm(f)
+
+
+@pytest.mark.parametrize("name,I,ny,nx,Q,per_col", [
+    ("sparse", 524288, 128, 128, 64, 4),    # more than 1024 rows per wave beside more than 8188 columns
+])
+def test_automatic_schedule_matches_oracle(name, I, ny, nx, Q, per_col):
+    """Past the small scans, with the schedule that the model takes."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import oracle
+    from paper_1601_08201_amd import sgtv
+    J = ny * nx * Q
+    rng = np.random.default_rng(9)
+    rows = rng.integers(0, I, (J, per_col))
+    A = sp.csr_matrix((rng.random(J * per_col).astype(np.float32) + 0.01,
+                       (rows.ravel(), np.repeat(np.arange(J), per_col))), shape=(I, J))
+    y, r = rng.poisson(5.0, I).astype(np.float32), np.full(I, 0.1, np.float32)
+    rowptr = A.indptr.astype(np.int64)
+    R = sgtv.Reconstructor(device=0)
+    R.set_system(I, ny, nx, Q, rowptr, A.indices, A.data).set_data(y, r, 0.1, 1.0)
+    image, sched = R.iterate(3).image(), R.schedule()
+    R.close()
+    assert sched["fwd_rows_per_wave"] > 1024
+    p = SimpleNamespace(ny=ny, nx=nx, Q=Q, I=I, J=J, rowptr=rowptr, col=A.indices, val=A.data, y=y, r=r, beta=0.1,
+                        rho=1.0, sweeps=1)
     f = oracle.admm(p, 3, report=False)[0]
     assert np.linalg.norm(image - f) <= 1e-5 * np.linalg.norm(f)
