@@ -290,7 +290,7 @@ TileParams choose_tiles(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_b
     // 16380 = the widest block of the 24-bit index format (a multiple of 4
     // below 2^14, leaving one code for the zero slot)
     t.cb = cb > 0 ? cb : static_cast<int>(std::min<int64_t>(16380, std::max<int64_t>(4, next_pow2(n_cols))));
-    if (cb <= 0 && rw <= 0 && n_cols > 16380) {
+    if (cb <= 0 && rw <= 0 && simple && n_cols > 16380) {
         // even blocks: with 16380 columns and a rest, the slab of the rest ends
         // early (16 scans of 9 x 41 x 54 in a batch, 19926 columns: 54.2 us an
         // iteration, with two blocks of 9964 50.7 us)
