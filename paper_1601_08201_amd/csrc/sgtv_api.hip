@@ -17,6 +17,7 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <queue>
 #include <string>
 #include <thread>
 #include <vector>
@@ -247,6 +248,93 @@ int64_t next_pow2(int64_t v) {
     return p;
 }
 
+// Entries of a matrix by place: sums over [0, i) x [0, j) of a grid of kLoadCells
+// cells a side, from up to kLoadSample entries spread evenly over the matrix
+// (counted by one thread in 3 to 25 ms, the choice with them takes 9 to 18 ms; 2 ms
+// where the entries are even).
+constexpr int kLoadCells = 256;
+constexpr int64_t kLoadSample = int64_t(1) << 20;
+
+struct LoadMap {
+    std::vector<double> sum;   // (kLoadCells + 1)^2, scaled to the whole matrix
+    int64_t step = 1;          // every step-th entry is counted
+    // entries in rows [0, r) and columns [0, c), both as fractions of the sides
+    double below(double r, double c) const {
+        const double y = std::min(r, 1.0) * kLoadCells, x = std::min(c, 1.0) * kLoadCells;
+        const int i = std::min(kLoadCells - 1, static_cast<int>(y)), j = std::min(kLoadCells - 1, static_cast<int>(x));
+        const double *p = sum.data() + i * (kLoadCells + 1) + j, fy = y - i, fx = x - j;
+        return (1 - fy) * ((1 - fx) * p[0] + fx * p[1]) +
+               fy * ((1 - fx) * p[kLoadCells + 1] + fx * p[kLoadCells + 2]);
+    }
+    LoadMap transposed() const {
+        LoadMap t;
+        t.step = step;
+        t.sum.resize(sum.size());
+        for (int i = 0; i <= kLoadCells; ++i)
+            for (int j = 0; j <= kLoadCells; ++j) t.sum[j * (kLoadCells + 1) + i] = sum[i * (kLoadCells + 1) + j];
+        return t;
+    }
+};
+
+LoadMap load_map(int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp, const std::vector<int32_t> &ci) {
+    constexpr int n = kLoadCells + 1;
+    LoadMap M;
+    M.sum.assign(n * n, 0.0);
+    const int64_t nnz = rp[n_rows];
+    const int64_t step = M.step = std::max<int64_t>(1, nnz / kLoadSample) | 1;   // odd: out of step with even row lengths
+    for (int64_t r = 0, k = 0; r < n_rows && k < nnz; ++r)
+        for (; k < rp[r + 1]; k += step)
+            M.sum[(r * kLoadCells / n_rows + 1) * n + ci[k] * int64_t(kLoadCells) / n_cols + 1] += static_cast<double>(step);
+    for (int i = 1; i < n; ++i)
+        for (int j = 1; j < n; ++j) M.sum[i * n + j] += M.sum[i * n + j - 1];
+    for (int i = 1; i < n; ++i)
+        for (int j = 1; j < n; ++j) M.sum[i * n + j] += M.sum[(i - 1) * n + j];
+    return M;
+}
+
+constexpr double kCus = 256.0;
+
+// The tiles of schedule t on the CUs, one per CU in the order of the launch:
+// when the last one ends, in us.  tile_us: time of a tile with no entries; the
+// entries of a tile cost its waves 0.17 us per group of 64 each.  Returns 0 where
+// the fullest tile holds at most a tenth more than its even share: then every
+// tile takes as long as the others, and rounds of 256 are all there is to count.
+double uneven_us(const LoadMap &M, int64_t n_rows, int64_t n_cols, int64_t nnz, const TileParams &t, double tile_us) {
+    const int64_t rb = static_cast<int64_t>(t.waves) * t.rw, n_rb = (n_rows + rb - 1) / rb;
+    const int64_t ncb = (n_cols + t.cb - 1) / t.cb;
+    std::vector<double> load(static_cast<size_t>(n_rb * t.ns)), edge(static_cast<size_t>(t.ns + 1)), above(edge.size(), 0.0);
+    for (int k = 0; k <= t.ns; ++k) edge[k] = std::min(1.0, static_cast<double>(k * ncb / t.ns * t.cb) / n_cols);
+    bool even = true;
+    for (int64_t b = 0; b < n_rb; ++b) {
+        const double r = std::min(1.0, static_cast<double>((b + 1) * rb) / n_rows);
+        double left = 0.0;
+        for (int k = 0; k < t.ns; ++k) {
+            const double at = M.below(r, edge[k + 1]), e = at - left - above[k + 1] + (k ? above[k] : 0.0);
+            load[b * t.ns + k] = e;
+            // a tenth, and four standard deviations of the sampled count
+            const double share = nnz * (static_cast<double>(rb) / n_rows) * (edge[k + 1] - edge[k]);
+            even = even && e <= 1.1 * share + 4.0 * std::sqrt(share * M.step);
+            if (k) above[k] = left;
+            left = at;
+        }
+        above[t.ns] = left;
+    }
+    if (even) return 0.0;
+    std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+    double end = 0.0;
+    for (const double e : load) {
+        double at = 0.0;
+        if (free_at.size() >= static_cast<size_t>(kCus)) {
+            at = free_at.top();
+            free_at.pop();
+        }
+        at += tile_us + 0.17 * e / (64.0 * t.waves);
+        free_at.push(at);
+        end = std::max(end, at);
+    }
+    return end;
+}
+
 // Modelled time in us of one product of a matrix of n_rows x n_cols with nnz
 // entries under schedule t, 16 waves, one workgroup per CU.  Fitted to 128^3
 // with 32 and 64 entries per column, 64^3 with 32 and 77 x 101 x 93 with 48
@@ -255,9 +343,13 @@ int64_t next_pow2(int64_t v) {
 // group of every wave 0.17 us (a list has one group more than its share); the
 // entries of all tiles pass no faster than 5.8 TB/s; and every slab writes a
 // partial sum per row that the next kernel reads one after the other, at about
-// 5 TB/s and 0.12 us each.
-double modelled_us(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_bytes, const TileParams &t) {
-    constexpr double kCus = 256.0;
+// 5 TB/s and 0.12 us each.  M (or null: an even matrix) says where the entries
+// are; with one tile holding most of a row block, low tiles in several rounds are
+// faster than one round of tall ones (128^3, 32 and 64 per column, every voxel in
+// a tenth of the detector: 1561 and 1024 rows per wave 477 and 773 us an
+// iteration, the 512 and 256 rows taken now 354 and 514 us).
+double modelled_us(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_bytes, const TileParams &t,
+                   const LoadMap *M = nullptr) {
     const double rb = static_cast<double>(t.waves) * t.rw;
     const double tiles = std::ceil(n_rows / rb) * t.ns;
     const double blocks = std::ceil(std::ceil(static_cast<double>(n_cols) / t.cb) / t.ns);
@@ -265,7 +357,12 @@ double modelled_us(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_bytes,
     const double entries = static_cast<double>(nnz) / n_rows / n_cols * std::min<double>(t.rw, static_cast<double>(n_rows)) * cols;
     const double tile = 8.0 + blocks * (0.64 + 3.6e-5 * cols + 0.17 * (entries / 64.0 + 1.0));
     const double stream = static_cast<double>(nnz) * (2.2 + value_bytes) / 5.8e6;
-    return std::max(std::ceil(tiles / kCus) * tile, stream) + t.ns * (0.12 + 8.0 * n_rows / 5.0e6);
+    double run = std::ceil(tiles / kCus) * tile;
+    if (M) {
+        const double u = uneven_us(*M, n_rows, n_cols, nnz, t, 8.0 + blocks * (0.64 + 3.6e-5 * cols + 0.17));
+        if (u > 0.0) run = u;
+    }
+    return std::max(run, stream) + t.ns * (0.12 + 8.0 * n_rows / 5.0e6);
 }
 
 // Automatic schedule: of the tile heights that fill whole rounds of the 256 CUs
@@ -284,7 +381,7 @@ bool modelled(int64_t nnz, int waves, int rw, bool simple) {
 }
 
 TileParams choose_tiles(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_bytes, int waves, int rw, int cb,
-                        int ns, bool simple = true) {
+                        int ns, bool simple = true, const LoadMap *M = nullptr) {
     TileParams t;
     t.waves = waves > 0 ? waves : 16;
     // 16380 = the widest block of the 24-bit index format (a multiple of 4
@@ -342,7 +439,7 @@ TileParams choose_tiles(int64_t n_rows, int64_t n_cols, int64_t nnz, int value_b
                 if (need > rw_max) continue;
                 const TileParams q{static_cast<int>(std::max<int64_t>(64, need)), 16, cc, slabs};
                 if (!streams && !sgtv::idx24_fits(q.rw, q.cb)) continue;
-                const double us = modelled_us(n_rows, n_cols, nnz, value_bytes, q);
+                const double us = modelled_us(n_rows, n_cols, nnz, value_bytes, q, M);
                 if (best_us == 0.0 || us < 0.99 * best_us) {
                     best = q;
                     best_us = us;
@@ -1625,10 +1722,15 @@ int pack_system(sgtv_ctx_s *c, Packed &PK, int64_t I, int32_t ny, int32_t nx, in
         const sgtv_schedule &q = c->want;
         const int vb = vt == SGTV_F32 ? 4 : 2;
         const bool var1 = q.variant <= 1;   // the simple loop, the only one on streamed and 24-bit lists
+        LoadMap mf, mb;
+        if (modelled(nnz, q.waves > 0 ? q.waves : 16, std::min(q.fwd_rows_per_wave, q.back_rows_per_wave), var1)) {
+            mf = load_map(I, J, rp, ci);
+            mb = mf.transposed();
+        }
         const TileParams tf = choose_tiles(I, J, nnz, vb, q.waves, q.fwd_rows_per_wave, q.fwd_block_cols, q.fwd_slabs,
-                                           var1);
+                                           var1, &mf);
         const TileParams tb = choose_tiles(J, I, nnz, vb, q.waves, q.back_rows_per_wave, q.back_block_cols, q.back_slabs,
-                                           var1);
+                                           var1, &mb);
         if (tile_lds_bytes(tf, var1) > 163840 || tile_lds_bytes(tb, var1) > 163840)
             return fail(SGTV_EINVAL, "schedule needs more than 160 KiB of LDS per workgroup");
         S->sched.waves = tf.waves;

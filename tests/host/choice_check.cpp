@@ -4,7 +4,8 @@
 //     reads them;
 //   * a tiled copy that ends in 32-bit lists (streaming refused, tiles too tall and
 //     wide for 24 bits) gives the row sums, walked as the kernel does;
-//   * the automatic schedule of sparse matrices ends in streamed lists.
+//   * the automatic schedule of sparse matrices ends in streamed lists, that of a
+//     matrix whose entries lie in a band takes lower tiles.
 // Prints one line per case and "ok" at the end; exits 1 after a failure.
 #include "../../paper_1601_08201_amd/csrc/sgtv_api.hip"
 
@@ -25,9 +26,10 @@ uint64_t lcg(uint64_t &s) {
     return s >> 33;
 }
 
-// len(r) entries in row r, in uniform columns
+// len(r) entries in row r, in uniform columns; band: in a tenth of the columns
+// that moves on with the row
 template <class Len>
-Csr make_csr(int64_t n_rows, int64_t n_cols, uint64_t seed, Len len) {
+Csr make_csr(int64_t n_rows, int64_t n_cols, uint64_t seed, Len len, bool band = false) {
     Csr m;
     m.n_rows = n_rows;
     m.n_cols = n_cols;
@@ -35,7 +37,8 @@ Csr make_csr(int64_t n_rows, int64_t n_cols, uint64_t seed, Len len) {
     uint64_t s = seed;
     for (int64_t r = 0; r < n_rows; ++r) {
         for (int64_t e = len(r); e > 0; --e) {
-            m.ci.push_back(static_cast<int32_t>(lcg(s) % n_cols));
+            m.ci.push_back(static_cast<int32_t>(band ? r * (n_cols - n_cols / 10) / n_rows + lcg(s) % (n_cols / 10)
+                                                     : lcg(s) % n_cols));
             m.v.push_back(static_cast<float>(lcg(s) % 1000 + 1) / 997.0f);
         }
         std::sort(m.ci.begin() + m.rp.back(), m.ci.end());
@@ -116,14 +119,19 @@ void check_lists32(const char *name, const Csr &m, TileParams t) {
 }
 
 // The automatic schedule of a product and the format its copy gets.
-void check_automatic(const char *name, const Csr &m, int want) {
+void check_automatic(const char *name, const Csr &m, int want, int tallest) {
     const int64_t nnz = m.rp[m.n_rows];
-    const TileParams t = choose_tiles(m.n_rows, m.n_cols, nnz, 4, 0, 0, 0, 0);
+    const LoadMap loads = load_map(m.n_rows, m.n_cols, m.rp, m.ci);
+    const TileParams t = choose_tiles(m.n_rows, m.n_cols, nnz, 4, 0, 0, 0, 0, true, &loads);
+    const TileParams even = choose_tiles(m.n_rows, m.n_cols, nnz, 4, 0, 0, 0, 0);
     PackedTiled T;
     CHECK(pack_tiled(T, m.n_rows, m.n_cols, m.rp, m.ci, m.v, t, true) == SGTV_OK, "%s: packing failed", name);
     const double bytes = 4.0 * (T.pk.size() + T.v32.size() + T.goff.size() + T.poff.size());
-    std::printf("%s: %d x %d, %d slabs, format %d, %.2f bytes an entry\n", name, t.rw, t.cb, t.ns, T.map.idx24, bytes / nnz);
+    std::printf("%s: %d x %d, %d slabs (even entries: %d x %d, %d), format %d, %.2f bytes an entry\n", name, t.rw, t.cb,
+                t.ns, even.rw, even.cb, even.ns, T.map.idx24, bytes / nnz);
     CHECK(want < 0 || T.map.idx24 == want, "%s: format %d", name, T.map.idx24);
+    CHECK(t.rw <= tallest, "%s: %d rows per wave", name, t.rw);
+    if (tallest >= 2048) CHECK(t.rw == even.rw && t.cb == even.cb && t.ns == even.ns, "%s: not the even schedule", name);
 }
 
 void check_rules() {
@@ -144,14 +152,16 @@ int main() {
     check_memory();
     check_rules();
     const int S = sgtv::kIdxStream;
-    check_automatic("128^3, 4 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 8; }), S);
-    check_automatic("128^3, 8 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 16; }), S);
-    check_automatic("128^3, 8 a voxel, back", make_csr(1 << 21, 1 << 20, 3, [](int64_t) { return 8; }), S);
-    check_automatic("128^3, 16 a voxel", make_csr(1 << 20, 1 << 21, 4, [](int64_t) { return 32; }), S);
-    check_automatic("100 x 100 x 110, 16 a voxel", make_csr(800000, 1100000, 5, [](int64_t) { return 22; }), S);
-    check_automatic("120 x 110 x 90, 20 a voxel, back", make_csr(1188000, 1000000, 6, [](int64_t) { return 20; }), S);
-    check_automatic("128 x 128 x 64, 8 a voxel", make_csr(524288, 1048576, 7, [](int64_t) { return 16; }), S);
-    check_automatic("96^3, 16 a voxel", make_csr(442368, 884736, 8, [](int64_t) { return 32; }), -1);
+    check_automatic("128^3, 4 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 8; }), S, 2048);
+    check_automatic("128^3, 8 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 16; }), S, 2048);
+    check_automatic("128^3, 8 a voxel, back", make_csr(1 << 21, 1 << 20, 3, [](int64_t) { return 8; }), S, 2048);
+    check_automatic("128^3, 16 a voxel", make_csr(1 << 20, 1 << 21, 4, [](int64_t) { return 32; }), S, 2048);
+    check_automatic("100 x 100 x 110, 16 a voxel", make_csr(800000, 1100000, 5, [](int64_t) { return 22; }), S, 2048);
+    check_automatic("120 x 110 x 90, 20 a voxel, back", make_csr(1188000, 1000000, 6, [](int64_t) { return 20; }), S, 2048);
+    check_automatic("128 x 128 x 64, 8 a voxel", make_csr(524288, 1048576, 7, [](int64_t) { return 16; }), S, 2048);
+    check_automatic("128^3, 8 a voxel in a band", make_csr(1 << 20, 1 << 21, 9, [](int64_t) { return 16; }, true), S, 1024);
+    check_automatic("64^3, 32 a voxel in a band", make_csr(131072, 262144, 9, [](int64_t) { return 64; }, true), -1, 256);
+    check_automatic("96^3, 16 a voxel", make_csr(442368, 884736, 8, [](int64_t) { return 32; }), -1, 2048);
     check_lists32("even rows", make_csr(40000, 50000, 1, [](int64_t) { return 3; }), TileParams{1500, 16, 15000, 2});
     check_lists32("uneven rows", make_csr(60001, 70001, 2, [](int64_t r) { return r % 9 == 4 ? 0 : 1 + r % 70; }),
                   TileParams{1400, 16, 16000, 3});
