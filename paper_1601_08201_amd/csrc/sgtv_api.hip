@@ -1542,30 +1542,49 @@ bool small_scan(const sgtv_ctx_s *c, int64_t I, int64_t J, int64_t nnz, const sg
 // Longest line of a small scan's copy: one lane walks it alone.
 constexpr int64_t kSmallLine = 192;
 
-// The second copy of a small scan: lines of entries in the order in which the
-// tiled product of map M adds them (column block after column block), the first
-// entry of every slab but a line's first marked by kSmallCut in its index.
-// lines: the line of M at every position.  False: a line is too long.
-template <class V>
-bool pack_small_side(const sgtv::TileMap &M, const std::vector<int64_t> &lptr, const std::vector<int32_t> &lidx,
-                     const std::vector<V> &lval, const std::vector<int64_t> &lines, std::vector<int64_t> &sptr,
-                     std::vector<int32_t> &idx, std::vector<V> &val) {
+// Where the second copy is taken: iterations on it are modelled at 8.5 us, 3.5 us
+// per million entries of either side and 1.4 us per million of padding, those on
+// tiles by their products and 6 us; and it takes at most three times the memory of
+// the tiles. Slices of 64 columns are as deep as their longest. 64^3 with 40
+// entries in every 64th voxel and 2 in the others, 0.7 M stored as 11 M: 27 us an
+// iteration, 41 on tiles; 150 in every 64th and 2, 1.1 M stored as 40 M in 320 MB:
+// 76 and 48; 60 in every 16th and 4, 2.0 M stored as 18 M: 40 and 43, but 3.2 times
+// the memory of the tiles, so left out.
+bool small_copy_pays(double entries, double stored, double value_bytes, double tiles_us, double tile_bytes) {
+    return 8.5 + 7e-6 * entries + 1.4e-6 * (stored - 2.0 * entries) <= tiles_us + 6.0 &&
+           stored * (4.0 + value_bytes) <= 3.0 * tile_bytes + 1048576.0;
+}
+
+// Slices of the lines' entries (sptr) of a small scan's copy; false: a line is too long.
+bool small_slices(const std::vector<int64_t> &lptr, const std::vector<int64_t> &lines, std::vector<int64_t> &sptr) {
     const int64_t n = static_cast<int64_t>(lines.size()), n_slices = (n + 63) / 64;
-    auto len_of = [&](int64_t k) { return lptr[lines[k] + 1] - lptr[lines[k]]; };
     sptr.assign(static_cast<size_t>(n_slices + 1), 0);
     for (int64_t sl = 0; sl < n_slices; ++sl) {
         int64_t width = 0;
-        for (int64_t k = sl * 64; k < std::min(n, (sl + 1) * 64); ++k) width = std::max(width, len_of(k));
+        for (int64_t k = sl * 64; k < std::min(n, (sl + 1) * 64); ++k)
+            width = std::max(width, lptr[lines[k] + 1] - lptr[lines[k]]);
         if (width > kSmallLine) return false;
         sptr[sl + 1] = sptr[sl] + (width + 3) / 4 * 4 * 64;
     }
+    return true;
+}
+
+// The second copy of a small scan: lines of entries in the order in which the
+// tiled product of map M adds them (column block after column block), the first
+// entry of every slab but a line's first marked by kSmallCut in its index.
+// lines: the line of M at every position; sptr: their slices.
+template <class V>
+void pack_small_side(const sgtv::TileMap &M, const std::vector<int64_t> &lptr, const std::vector<int32_t> &lidx,
+                     const std::vector<V> &lval, const std::vector<int64_t> &lines, const std::vector<int64_t> &sptr,
+                     std::vector<int32_t> &idx, std::vector<V> &val) {
+    const int64_t n = static_cast<int64_t>(lines.size()), n_slices = (n + 63) / 64;
     idx.assign(static_cast<size_t>(sptr[n_slices]), sgtv::kSmallPad);
     val.assign(static_cast<size_t>(sptr[n_slices]), V(0));
     on_threads(n_slices, [&](int64_t first, int64_t step) {
         std::vector<int64_t> order;
         for (int64_t sl = first; sl < n_slices; sl += step)
             for (int64_t k = sl * 64; k < std::min(n, (sl + 1) * 64); ++k) {
-                const int64_t from = lptr[lines[k]], len = len_of(k);
+                const int64_t from = lptr[lines[k]], len = lptr[lines[k] + 1] - from;
                 const bool ascending = std::is_sorted(lidx.begin() + from, lidx.begin() + from + len);
                 if (!ascending) {
                     order.resize(static_cast<size_t>(len));
@@ -1586,26 +1605,37 @@ bool pack_small_side(const sgtv::TileMap &M, const std::vector<int64_t> &lptr, c
                 }
             }
     });
-    return true;
 }
 
+// Leaves the copy out where it does not pay or the tiles' lists are not
+// lane-owned (32-bit lists add in another order than the copy).
 template <class V>
 void pack_small(Packed &PK, const std::vector<int64_t> &rp, const std::vector<int32_t> &ci, const std::vector<V> &av,
                 const std::vector<int64_t> &cp, const std::vector<int32_t> &cidx, const std::vector<V> &cv) {
     System &S = *PK.S;
+    if (!PK.fwd.map.idx24 || !PK.back.map.idx24) return;
     // rows by decreasing length (stable): the 64 rows of a slice have nearly equal ones
     std::vector<int64_t> rows(static_cast<size_t>(S.I)), cols(static_cast<size_t>(S.J));
     for (int64_t i = 0; i < S.I; ++i) rows[i] = i;
     for (int64_t j = 0; j < S.J; ++j) cols[j] = j;
     std::stable_sort(rows.begin(), rows.end(),
                      [&](int64_t x, int64_t y) { return rp[x + 1] - rp[x] > rp[y + 1] - rp[y]; });
-    std::vector<V> rv, wv;
-    if (!pack_small_side(PK.fwd.map, rp, ci, av, rows, PK.rsp, PK.rsi, rv) ||
-        !pack_small_side(PK.back.map, cp, cidx, cv, cols, PK.csp, PK.csi, wv)) {
-        for (auto *v : {&PK.rsp, &PK.csp}) v->clear();
-        for (auto *v : {&PK.rsi, &PK.csi}) v->clear();
+    auto tiles_us = [&](const sgtv::TileMap &M) {
+        return modelled_us(M.n_rows, M.n_cols, S.nnz, sizeof(V), TileParams{M.rw, M.waves, M.cb, M.ns});
+    };
+    auto tile_bytes = [](const PackedTiled &T) {
+        return 4.0 * (T.pk.size() + T.v32.size() + T.goff.size() + T.poff.size()) + 2.0 * (T.v16.size() + T.slot.size());
+    };
+    std::vector<int64_t> rsp, csp;
+    if (!small_slices(rp, rows, rsp) || !small_slices(cp, cols, csp) ||
+        !small_copy_pays(static_cast<double>(S.nnz), static_cast<double>(rsp.back() + csp.back()), sizeof(V),
+                         tiles_us(PK.fwd.map) + tiles_us(PK.back.map), tile_bytes(PK.fwd) + tile_bytes(PK.back)))
         return;
-    }
+    std::vector<V> rv, wv;
+    pack_small_side(PK.fwd.map, rp, ci, av, rows, rsp, PK.rsi, rv);
+    pack_small_side(PK.back.map, cp, cidx, cv, cols, csp, PK.csi, wv);
+    PK.rsp.swap(rsp);
+    PK.csp.swap(csp);
     S.n_rslices = static_cast<int64_t>(PK.rsp.size()) - 1;
     S.n_cslices = static_cast<int64_t>(PK.csp.size()) - 1;
     S.perm.swap(rows);

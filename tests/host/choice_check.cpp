@@ -4,6 +4,7 @@
 //     reads them;
 //   * a tiled copy that ends in 32-bit lists (streaming refused, tiles too tall and
 //     wide for 24 bits) gives the row sums, walked as the kernel does;
+//   * a small scan's second copy is left out where it would be mostly padding;
 //   * the automatic schedule of sparse matrices ends in streamed lists, that of a
 //     matrix whose entries lie in a band takes lower tiles.
 // Prints one line per case and "ok" at the end; exits 1 after a failure.
@@ -146,11 +147,45 @@ void check_rules() {
     std::printf("rules of the schedule\n");
 }
 
+// len(j) entries in voxel j of a scan of ny x nx x Q, in uniform measurements:
+// does it get the second copy of a small scan
+// (want 1, 0; -1 either)?
+template <class Len>
+void check_small(const char *name, int64_t I, int ny, int nx, int Q, int want, Len len) {
+    const Csr t = make_csr(static_cast<int64_t>(ny) * nx * Q, I, 11, len);
+    std::vector<int64_t> rp, lrp = t.rp;
+    std::vector<int32_t> ci;
+    std::vector<float> v;
+    transpose_csr(t.n_rows, I, t.rp, t.ci, t.v, rp, ci, v);
+    sgtv_ctx_s c;
+    Packed PK;
+    CHECK(pack_system(&c, PK, I, ny, nx, Q, rp.data(), ci.data(), v.data(), rp.back(), SGTV_F32, nullptr, 0, SGTV_HOST) ==
+              SGTV_OK, "%s: packing failed", name);
+    const double tiles = 8.0 * (PK.fwd.v32.size() + PK.back.v32.size());
+    const double copy = 8.0 * (PK.rsv32.size() + PK.csv32.size());
+    std::printf("%s: %lld entries, tiles %.1f MB, second copy %.1f MB\n", name, static_cast<long long>(rp.back()),
+                tiles / 1e6, copy / 1e6);
+    CHECK(want < 0 || PK.S->small() == (want == 1), "%s: %s", name, want ? "no second copy" : "a second copy");
+    CHECK(copy <= 3.3 * tiles + 1048576.0, "%s: second copy of %.0f MB", name, copy / 1e6);
+}
+
 }  // namespace
 
 int main() {
     check_memory();
     check_rules();
+    check_small("16 a voxel", 4096, 16, 16, 32, 1, [](int64_t) { return 16; });
+    check_small("24 a voxel", 8192, 9, 41, 54, 1, [](int64_t) { return 24; });
+    check_small("9 a voxel", 131072, 64, 64, 64, 1, [](int64_t) { return 9; });
+    check_small("1 a voxel", 131072, 64, 64, 64, 1, [](int64_t) { return 1; });
+    check_small("1 a voxel, 20000 measurements", 20000, 128, 128, 128, 1, [](int64_t) { return 1; });
+    check_small("one entry", 1, 1, 1, 1, 1, [](int64_t) { return 1; });
+    check_small("150 in every 64th voxel, 2 in the others", 131072, 64, 64, 64, 0,
+                [](int64_t j) { return j % 64 ? 2 : 150; });
+    check_small("150 in every 64th voxel", 131072, 64, 128, 100, 0, [](int64_t j) { return j % 64 ? 0 : 150; });
+    check_small("40 in every 64th voxel, 2 in the others", 131072, 64, 64, 64, 1, [](int64_t j) { return j % 64 ? 2 : 40; });
+    check_small("60 in every 16th voxel, 4 in the others", 131072, 64, 64, 64, -1,
+                [](int64_t j) { return j % 16 ? 4 : 60; });
     const int S = sgtv::kIdxStream;
     check_automatic("128^3, 4 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 8; }), S, 2048);
     check_automatic("128^3, 8 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 16; }), S, 2048);

@@ -145,3 +145,24 @@ def test_split_beside_ratio_equals_apart(sg, I, ny, nx, Q, weights, grouping, sw
         B.iterate(n)
         for a, b in zip(A.state()[:3], B.state()[:3]):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("deep,taken", [(40, True), (150, False)])
+def test_padding_of_uneven_columns_is_bounded(sg, deep, taken):
+    """Every 64th voxel with many entries, two in the others: slices of 64 columns are as deep as the longest. The copy
+    is left out where it is mostly padding; the images do not depend on it."""
+    I, ny, nx, Q = 131072, 64, 64, 64
+    J = ny * nx * Q
+    rng = np.random.default_rng(8)
+    cols = np.repeat(np.arange(J), np.where(np.arange(J) % 64 == 0, deep, 2))
+    rows = rng.integers(0, I, cols.size)
+    order = np.lexsort((cols, rows))
+    rowptr = np.zeros(I + 1, np.int64)
+    rowptr[1:] = np.bincount(rows, minlength=I).cumsum()
+    args = (I, ny, nx, Q, rowptr, cols[order].astype(np.int32), (rng.random(cols.size) + 0.01).astype(np.float32))
+    y, r = rng.poisson(6.0, I).astype(np.float32), np.full(I, 0.1, np.float32)
+    A = sg.Reconstructor().set_system(*args).set_data(y, r, 0.2, 1.0)
+    T = sg.Reconstructor().set_schedule(**A.schedule()).set_system(*args).set_data(y, r, 0.2, 1.0)
+    copy = A.device_bytes() - T.device_bytes()
+    assert (copy > 0) == taken and copy <= 3 * T.device_bytes()
+    np.testing.assert_array_equal(A.iterate(5).image(), T.iterate(5).image())
