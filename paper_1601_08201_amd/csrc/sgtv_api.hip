@@ -3207,30 +3207,49 @@ int64_t sgtv_workspace_bytes(int64_t I, int64_t J, int64_t nnz, int storage_dtyp
     if (I < 0 || J < 0 || nnz < 0) return -1;
     if (storage_dtype != SGTV_F32 && storage_dtype != SGTV_BF16 && storage_dtype != SGTV_F16) return -1;
     const int64_t vb = storage_dtype == SGTV_F32 ? 4 : 2;
-    // one tiled copy with the automatic schedule: a list (rows of one wave x
-    // one column block) of E entries takes max(E / 64 + 1, longest row run)
-    // groups of 64, the run estimated for rows with lam entries per block
+    // One tiled copy with the automatic schedule, its entries spread evenly: a list
+    // (rows of one wave x one column block) of e entries takes max(e / 64 + 1,
+    // longest row run) groups of 64, the run estimated for rows with lam entries per
+    // block. A streamed list takes its lanes' share, the padding of steps past dmax
+    // rows between two of a lane's runs (gaps between filled rows are geometric) and
+    // two thirds of a group, and 64 base rows of two bytes; the format is the one that
+    // stream_lists would take.
+    double tiles_us = 0.0;
     auto copy_bytes = [&](int64_t n_rows, int64_t n_cols, int64_t *slabs) -> double {
         const TileParams t = choose_tiles(n_rows, n_cols, nnz, static_cast<int>(vb), 16, 0, 0, 0);
         *slabs = t.ns;
         if (n_rows == 0 || n_cols == 0) return 0.0;
+        tiles_us += modelled_us(n_rows, n_cols, nnz, static_cast<int>(vb), t);
         const double n_rb = std::ceil(static_cast<double>(n_rows) / (16.0 * t.rw));
         const double ncb = std::ceil(static_cast<double>(n_cols) / t.cb);
         const double lists = n_rb * ncb * 16.0;
         const double lam = static_cast<double>(nnz) / n_rows * std::min<double>(t.cb, n_cols) / n_cols;
         const double e = static_cast<double>(nnz) / lists;
-        const double groups = std::max(std::ceil(e / 64.0) + 1.0, std::ceil(lam + 2.5 * std::sqrt(lam) + 1.0));
+        const double run = std::ceil(lam + 2.5 * std::sqrt(lam) + 1.0);
+        const double groups = std::max(std::ceil(e / 64.0) + 1.0, run);
+        const bool narrow = sgtv::idx24_fits(t.rw, t.cb);
+        const double slots = 2.0 * n_rb * 16.0 * t.rw * t.ns;   // the row order of every tile
+        const double dense = std::max({e / 64.0 + 0.5, run, 1.0});
+        const double other = lists * (64.0 * dense * ((narrow ? 3 : 4) + vb) + 8.0);
+        if (lam > 0.0 && std::ceil(ncb / t.ns) >= sgtv::kStreamBlocks && sgtv::stream_fits(t.rw, t.cb, 16)) {
+            const double dmax = (1 << (16 - sgtv::stream_col_bits(t.cb, 16))) - 1;
+            const double q = std::exp(-lam), qd = std::pow(q, dmax), rows = t.rw * (1.0 - q) / 64.0;   // filled, a lane
+            const double pads = (1.0 - q) / lam * qd / (1.0 - qd) * std::max(0.0, 1.0 - 1.0 / rows);
+            const double share = std::max(e / 64.0 * (1.0 + pads), 1.0) + 0.67;
+            const double chunks = 0.5 * sgtv::kStreamChunk * t.ns / ncb;   // ends of streams
+            const double kept = lists * (64.0 * (share + chunks) * (2.0 + vb) + 132.0);
+            if (!(narrow && share > 1.35 * dense) && kept <= (narrow ? 1.35 : 2.0) * other) return kept + slots;
+        }
         const double stored = std::min(lists * 64.0 * groups, 64.0 * static_cast<double>(nnz) + 256.0);
-        // the automatic schedule streams its lists: two-byte indices and 64
-        // two-byte base rows a list, and the row order of every tile (2 bytes
-        // per row and slab)
-        const double idx_bytes = 2.0;
-        const double order = lists * 128.0 + 2.0 * n_rb * 16.0 * t.rw * t.ns;
-        return stored * (idx_bytes + vb) + lists * 8.0 + order;
+        return stored * ((narrow ? 3.0 : 4.0) + vb) + lists * 8.0 + (narrow ? slots : 0.0);
     };
     int64_t ns_f = 1, ns_b = 1;
     double matrix = copy_bytes(I, J, &ns_f) + copy_bytes(J, I, &ns_b);
-    if (nnz < kSmallScan) matrix += 2.3 * static_cast<double>(nnz) * (4.0 + vb) + 4.0 * I;   // small_scan
+    if (nnz > 0 && nnz < kSmallScan && I > 0 && J > 0) {   // the second copy (small_scan, pack_small)
+        const double stored = nnz + 2.0 * I + J * (std::ceil(nnz / (4.0 * J)) * 4.0);
+        if (small_copy_pays(static_cast<double>(nnz), stored, static_cast<double>(vb), tiles_us, matrix))
+            matrix += stored * (4.0 + vb) + 4.0 * I;
+    }
     const int64_t vectors = 4 * (3 * J + 2 * 4 * J + 2 * J + 2 * J)   // f x2, fs, v x2, a x2, sens, H
                             + 4 * 3 * I                                   // y, r, ratio
                             + 4 * (ns_f * I + ns_b * J)                   // partial sums

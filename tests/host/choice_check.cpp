@@ -4,7 +4,8 @@
 //     reads them;
 //   * a tiled copy that ends in 32-bit lists (streaming refused, tiles too tall and
 //     wide for 24 bits) gives the row sums, walked as the kernel does;
-//   * a small scan's second copy is left out where it would be mostly padding;
+//   * a small scan's second copy is left out where it would be mostly padding, and
+//     the memory estimate follows the formats that are taken;
 //   * the automatic schedule of sparse matrices ends in streamed lists, that of a
 //     matrix whose entries lie in a band takes lower tiles.
 // Prints one line per case and "ok" at the end; exits 1 after a failure.
@@ -151,7 +152,7 @@ void check_rules() {
 // does it get the second copy of a small scan
 // (want 1, 0; -1 either)?
 template <class Len>
-void check_small(const char *name, int64_t I, int ny, int nx, int Q, int want, Len len) {
+void check_small(const char *name, int64_t I, int ny, int nx, int Q, int want, Len len, bool even = true) {
     const Csr t = make_csr(static_cast<int64_t>(ny) * nx * Q, I, 11, len);
     std::vector<int64_t> rp, lrp = t.rp;
     std::vector<int32_t> ci;
@@ -167,6 +168,16 @@ void check_small(const char *name, int64_t I, int ny, int nx, int Q, int want, L
                 tiles / 1e6, copy / 1e6);
     CHECK(want < 0 || PK.S->small() == (want == 1), "%s: %s", name, want ? "no second copy" : "a second copy");
     CHECK(copy <= 3.3 * tiles + 1048576.0, "%s: second copy of %.0f MB", name, copy / 1e6);
+    if (!even) return;
+    // the estimate of the memory that is held, within a quarter
+    double held = 4.0 * (3 * t.n_rows + 8 * t.n_rows + 4 * t.n_rows + 3 * I) + 4.0 * (PK.fpart_floats + PK.bpart_floats) +
+                  8.0 * (PK.rsv32.size() + PK.csv32.size()) + 1048576.0;
+    for (const PackedTiled *T : {&PK.fwd, &PK.back})
+        held += 4.0 * (T->pk.size() + T->v32.size() + T->goff.size() + T->poff.size()) + 2.0 * T->slot.size();
+    const double est = static_cast<double>(sgtv_workspace_bytes(I, t.n_rows, rp.back(), SGTV_F32));
+    std::printf("%s: held %.1f MB, estimate %.1f MB, formats %d %d\n", name, held / 1e6, est / 1e6, PK.fwd.map.idx24,
+                PK.back.map.idx24);
+    CHECK(std::fabs(est - held) <= 0.25 * held, "%s: estimate", name);
 }
 
 }  // namespace
@@ -179,13 +190,19 @@ int main() {
     check_small("9 a voxel", 131072, 64, 64, 64, 1, [](int64_t) { return 9; });
     check_small("1 a voxel", 131072, 64, 64, 64, 1, [](int64_t) { return 1; });
     check_small("1 a voxel, 20000 measurements", 20000, 128, 128, 128, 1, [](int64_t) { return 1; });
+    check_small("32 a voxel", 131072, 64, 64, 64, 0, [](int64_t) { return 32; });
+    check_small("8 a voxel, 128 x 128 x 64", 524288, 128, 128, 64, 0, [](int64_t) { return 8; });
+    check_small("8 a voxel, 128^3", 1 << 20, 128, 128, 128, 0, [](int64_t) { return 8; });
+    check_small("16 a voxel, 60 x 100 x 100", 600000, 60, 100, 100, 0, [](int64_t) { return 16; });
+    check_small("3 a voxel, 100 x 100 x 100", 400000, 100, 100, 100, 0, [](int64_t) { return 3; });
+    check_small("24 a voxel, 77 x 101 x 40", 150001, 77, 101, 40, 0, [](int64_t) { return 24; });
     check_small("one entry", 1, 1, 1, 1, 1, [](int64_t) { return 1; });
     check_small("150 in every 64th voxel, 2 in the others", 131072, 64, 64, 64, 0,
-                [](int64_t j) { return j % 64 ? 2 : 150; });
-    check_small("150 in every 64th voxel", 131072, 64, 128, 100, 0, [](int64_t j) { return j % 64 ? 0 : 150; });
-    check_small("40 in every 64th voxel, 2 in the others", 131072, 64, 64, 64, 1, [](int64_t j) { return j % 64 ? 2 : 40; });
+                [](int64_t j) { return j % 64 ? 2 : 150; }, false);
+    check_small("150 in every 64th voxel", 131072, 64, 128, 100, 0, [](int64_t j) { return j % 64 ? 0 : 150; }, false);
+    check_small("40 in every 64th voxel, 2 in the others", 131072, 64, 64, 64, 1, [](int64_t j) { return j % 64 ? 2 : 40; }, false);
     check_small("60 in every 16th voxel, 4 in the others", 131072, 64, 64, 64, -1,
-                [](int64_t j) { return j % 16 ? 4 : 60; });
+                [](int64_t j) { return j % 16 ? 4 : 60; }, false);
     const int S = sgtv::kIdxStream;
     check_automatic("128^3, 4 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 8; }), S, 2048);
     check_automatic("128^3, 8 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 16; }), S, 2048);
