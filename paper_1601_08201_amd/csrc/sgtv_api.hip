@@ -1144,20 +1144,33 @@ int stream_lists(const TileLists &P, const std::vector<int32_t> &ci, const std::
     return SGTV_OK;
 }
 
+// One tiled copy.  simple: for the simple loop, which reads streamed lists (where
+// stream allows them, the tile fits them and they pay), else 24-bit ones where the
+// tile fits those; the other loops read 32-bit lists.
 template <class V>
 int build_tiled(int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp,
                 const std::vector<int32_t> &ci, const std::vector<V> &vals, const TileParams &t,
-                bool idx24, std::vector<int32_t> &pk, std::vector<V> &pv, std::vector<int32_t> &goff,
-                std::vector<int32_t> &poff, std::vector<uint16_t> &slot_of, sgtv::TileMap &map) {
+                bool simple, std::vector<int32_t> &pk, std::vector<V> &pv, std::vector<int32_t> &goff,
+                std::vector<int32_t> &poff, std::vector<uint16_t> &slot_of, sgtv::TileMap &map, bool stream = false) {
     // 24-bit indices: row in 10 bits and column in 14 (up to 1024 rows per
     // wave), or 11 and 13 (up to 2048), with the code cb left for the zero
     // slot.  Their lists are lane-owned: all entries of a row within a list sit
     // in one lane, in row order, so a lane can read every accumulator of a
     // window of entries at once (no other lane touches its rows)
-    idx24 = idx24 && sgtv::idx24_fits(t.rw, t.cb);
+    const bool idx24 = simple && sgtv::idx24_fits(t.rw, t.cb);
+    stream = stream && simple && sgtv::stream_fits(t.rw, t.cb, t.waves) &&
+             sgtv::tiled_lds_bytes(t.waves, t.rw, t.cb, true) <= 163840;
     TileLists P;
-    plan_lists(n_rows, n_cols, rp, ci, t, idx24, P);
-    const int e = place_lists(P, rp, ci, vals, idx24, pk, pv, goff, poff, map);
+    plan_lists(n_rows, n_cols, rp, ci, t, stream || idx24, P);
+    int e = SGTV_OK;
+    if (stream) e = stream_lists(P, ci, vals, idx24, pk, pv, goff, poff, map);
+    if (e == SGTV_OK && pk.empty()) {
+        if (stream && !idx24) {   // 32-bit lists hold the rows in their own order
+            P = TileLists{};
+            plan_lists(n_rows, n_cols, rp, ci, t, false, P);
+        }
+        e = place_lists(P, rp, ci, vals, idx24, pk, pv, goff, poff, map);
+    }
     slot_of.swap(P.slot_of);
     return e;
 }
@@ -1173,25 +1186,10 @@ struct PackedTiled {
 
 template <class V>
 int pack_tiled(PackedTiled &T, int64_t n_rows, int64_t n_cols, const std::vector<int64_t> &rp,
-               const std::vector<int32_t> &ci, const std::vector<V> &vals, const TileParams &t, bool idx24) {
+               const std::vector<int32_t> &ci, const std::vector<V> &vals, const TileParams &t, bool simple) {
     std::vector<V> pv;
-    // the simple loop reads streamed lists where the tile fits them and the
-    // matrix is dense enough, else 24-bit or 32-bit indices
-    const bool stream = idx24 && sgtv::stream_fits(t.rw, t.cb, t.waves) &&
-                        sgtv::tiled_lds_bytes(t.waves, t.rw, t.cb, true) <= 163840;
-    idx24 = idx24 && sgtv::idx24_fits(t.rw, t.cb);
-    TileLists P;
-    plan_lists(n_rows, n_cols, rp, ci, t, stream || idx24, P);
-    if (stream)
-        if (int e = stream_lists(P, ci, vals, idx24, T.pk, pv, T.goff, T.poff, T.map)) return e;
-    if (T.pk.empty()) {
-        if (stream && !idx24) {   // 32-bit lists hold the rows in their own order
-            P = TileLists{};
-            plan_lists(n_rows, n_cols, rp, ci, t, false, P);
-        }
-        if (int e = place_lists(P, rp, ci, vals, idx24, T.pk, pv, T.goff, T.poff, T.map)) return e;
-    }
-    T.slot.swap(P.slot_of);
+    if (int e = build_tiled(n_rows, n_cols, rp, ci, vals, t, simple, T.pk, pv, T.goff, T.poff, T.slot, T.map, true))
+        return e;
     if constexpr (sizeof(V) == 4) T.v32.swap(pv);
     else T.v16.swap(pv);
     return SGTV_OK;
