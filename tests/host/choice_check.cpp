@@ -180,11 +180,27 @@ void check_small(const char *name, int64_t I, int ny, int nx, int Q, int want, L
     CHECK(std::fabs(est - held) <= 0.25 * held, "%s: estimate", name);
 }
 
+void check_format(const char *name, const Csr &m, TileParams t, int want) {
+    PackedTiled T;
+    CHECK(pack_tiled(T, m.n_rows, m.n_cols, m.rp, m.ci, m.v, t, true) == SGTV_OK, "%s: packing failed", name);
+    CHECK(T.map.idx24 == want, "%s: format %d", name, T.map.idx24);
+    std::printf("%s: format %d\n", name, want);
+}
+
 }  // namespace
 
 int main() {
     check_memory();
     check_rules();
+    const int S = sgtv::kIdxStream;
+    // the shapes that tests/test_gpu_stream.py takes for streamed ones
+    check_format("13 bits, full block", make_csr(30000, 19926, 1, [](int64_t) { return 16; }), TileParams{64, 16, 4092, 1}, S);
+    check_format("14 bits, widest block, back", make_csr(35420, 50000, 1, [](int64_t) { return 24; }),
+                 TileParams{100, 16, 16380, 1}, S);
+    check_format("all of the LDS", make_csr(60000, 32768, 1, [](int64_t) { return 13; }), TileParams{2048, 16, 8188, 1}, S);
+    check_format("narrow blocks, slabs", make_csr(3001, 3003, 1, [](int64_t) { return 16; }), TileParams{65, 4, 256, 3}, S);
+    check_format("one wave, back", make_csr(930, 700, 1, [](int64_t) { return 9; }), TileParams{300, 1, 100, 1}, S);
+    check_format("one row, three blocks", make_csr(1, 768, 1, [](int64_t) { return 768; }), TileParams{64, 16, 256, 1}, S);
     check_small("16 a voxel", 4096, 16, 16, 32, 1, [](int64_t) { return 16; });
     check_small("24 a voxel", 8192, 9, 41, 54, 1, [](int64_t) { return 24; });
     check_small("9 a voxel", 131072, 64, 64, 64, 1, [](int64_t) { return 9; });
@@ -203,7 +219,8 @@ int main() {
     check_small("40 in every 64th voxel, 2 in the others", 131072, 64, 64, 64, 1, [](int64_t j) { return j % 64 ? 2 : 40; }, false);
     check_small("60 in every 16th voxel, 4 in the others", 131072, 64, 64, 64, -1,
                 [](int64_t j) { return j % 16 ? 4 : 60; }, false);
-    const int S = sgtv::kIdxStream;
+    check_automatic("128 x 128 x 64, 4 a voxel", make_csr(524288, 1048576, 3, [](int64_t) { return 8; }), S, 2048);
+    check_automatic("128 x 128 x 64, 4 a voxel, back", make_csr(1048576, 524288, 3, [](int64_t) { return 4; }), S, 2048);
     check_automatic("128^3, 4 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 8; }), S, 2048);
     check_automatic("128^3, 8 a voxel", make_csr(1 << 20, 1 << 21, 3, [](int64_t) { return 16; }), S, 2048);
     check_automatic("128^3, 8 a voxel, back", make_csr(1 << 21, 1 << 20, 3, [](int64_t) { return 8; }), S, 2048);

@@ -142,3 +142,26 @@ def test_automatic_schedule_matches_oracle(name, I, ny, nx, Q, per_col):
                         rho=1.0, sweeps=1)
     f = oracle.admm(p, 3, report=False)[0]
     assert np.linalg.norm(image - f) <= 1e-5 * np.linalg.norm(f)
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+def test_one_row_in_three_blocks(storage):
+    """One measurement that sees every voxel once: the forward list streams as one run a column block
+    (tests/test_host_choices.py asserts the format)."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import oracle
+    from paper_1601_08201_amd import sgtv
+    J = 768
+    val = np.random.default_rng(2).random(J).astype(np.float32) + np.float32(0.01)
+    p = SimpleNamespace(ny=4, nx=4, Q=48, I=1, J=J, rowptr=np.array([0, J], np.int64), col=np.arange(J, dtype=np.int32),
+                        val=val, y=np.array([40.0], np.float32), r=np.array([0.1], np.float32), beta=0.1, rho=1.0, sweeps=1)
+    R = sgtv.Reconstructor(device=0)
+    R.set_schedule(fwd_rows_per_wave=64, fwd_block_cols=256, fwd_slabs=1, back_rows_per_wave=64, back_block_cols=4)
+    R.set_system(1, 4, 4, 48, p.rowptr, p.col, p.val, storage=storage).set_data(p.y, p.r, 0.1, 1.0)
+    image = R.iterate(3).image()
+    R.close()
+    if storage != "f32":
+        p.val = oracle.quantise(p.col, p.val, J, storage)[2]
+    f = oracle.admm(p, 3, report=False)[0]
+    assert np.linalg.norm(image - f) <= 1e-5 * np.linalg.norm(f)
