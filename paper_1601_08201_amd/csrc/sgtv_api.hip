@@ -2576,6 +2576,16 @@ int move_arrays(int device, int fd, std::vector<DBuf *> &bufs, const std::vector
     return SGTV_OK;
 }
 
+// Sizes of a tiled copy's arrays (bytes, 0: absent) against its map. 32-bit lists
+// have no slot table: files that were saved with one hold rows that were dealt to
+// the waves but not placed so, and give wrong sums.
+bool tiles_consistent(const sgtv::TileMap &t, int64_t goff, int64_t poff, int64_t slot) {
+    const int64_t n_lists = t.n_rb * static_cast<int64_t>(t.ns) * t.cbs_max * t.waves;
+    return t.ns >= 1 && t.ns <= sgtv::kMaxSlabs && n_lists >= 0 && goff == 4 * (n_lists + 1) &&
+           (t.idx24 != sgtv::kIdxStream || poff == 4 * (t.n_rb * t.ns * t.waves + 1 + 32 * n_lists)) &&
+           (slot == 0 || (t.idx24 != 0 && slot == 2 * t.n_rb * t.ns * t.waves * t.rw));
+}
+
 std::vector<char> head_bytes(const FileHead &fh, const SysMeta &m, const std::vector<int64_t> &perm,
                              const std::vector<ArrayRec> &rec) {
     std::vector<char> b(sizeof(fh) + sizeof(m) + sizeof(int64_t) * perm.size() + sizeof(ArrayRec) * rec.size());
@@ -2718,15 +2728,12 @@ int sgtv_load_system(sgtv_ctx ctx, const char *path) {
         bool sizes_ok = rec_of(S.H).bytes == 4 * S.J && rec_of(S.htab).bytes == 64 &&
                         (S.vt == SGTV_F32 || rec_of(S.colscale).bytes == 4 * S.J) &&
                         (!S.wfull || rec_of(S.wbuf).bytes == 16 * S.J);
-        if (S.format == SGTV_FORMAT_TILED)
-            for (const Tiled *T : {&S.fwd, &S.back}) {
-                const sgtv::TileMap &t = T->map;
-                const int64_t n_lists = t.n_rb * static_cast<int64_t>(t.ns) * t.cbs_max * t.waves;
-                sizes_ok = sizes_ok && t.ns >= 1 && t.ns <= sgtv::kMaxSlabs && n_lists >= 0 &&
-                           rec_of(T->goff).bytes == 4 * (n_lists + 1) &&
-                           (t.idx24 != sgtv::kIdxStream ||
-                            rec_of(T->poff).bytes == 4 * (t.n_rb * t.ns * t.waves + 1 + 32 * n_lists));
-            }
+        if (S.format == SGTV_FORMAT_TILED) {
+            for (const Tiled *T : {&S.fwd, &S.back})
+                sizes_ok = sizes_ok && tiles_consistent(T->map, rec_of(T->goff).bytes, rec_of(T->poff).bytes,
+                                                        rec_of(T->slot).bytes);
+            sizes_ok = sizes_ok && m.fpart_bytes >= 4 * S.I * S.fwd.map.ns && m.bpart_bytes >= 4 * S.J * S.back.map.ns;
+        }
         if (S.small()) {   // the second copy of a small scan: lines of rows (permuted) and columns
             const int64_t nr = (S.I + 63) / 64, nc = (S.J + 63) / 64;
             const int64_t vb = S.vt == SGTV_F32 ? 4 : 2;

@@ -117,6 +117,9 @@ void check_lists32(const char *name, const Csr &m, TileParams t) {
     for (size_t i = 0; i < ref.size(); ++i)
         CHECK(std::fabs(got[i] - ref[i]) <= 1e-9 * (1.0 + std::fabs(ref[i])), "%s: row %lld", name,
               static_cast<long long>(i) % static_cast<long long>(m.n_rows));
+    // saved copies of this format with dealt rows are refused
+    const int64_t goff = 4 * static_cast<int64_t>(T.goff.size());
+    CHECK(tiles_consistent(M, goff, 0, 0) && !tiles_consistent(M, goff, 0, 2 * M.n_rb * M.ns * RB), "%s: sizes", name);
     std::printf("%s: 32-bit lists\n", name);
 }
 
@@ -184,6 +187,7 @@ void check_format(const char *name, const Csr &m, TileParams t, int want) {
     PackedTiled T;
     CHECK(pack_tiled(T, m.n_rows, m.n_cols, m.rp, m.ci, m.v, t, true) == SGTV_OK, "%s: packing failed", name);
     CHECK(T.map.idx24 == want, "%s: format %d", name, T.map.idx24);
+    CHECK(tiles_consistent(T.map, 4 * T.goff.size(), 4 * T.poff.size(), 2 * T.slot.size()), "%s: sizes", name);
     std::printf("%s: format %d\n", name, want);
 }
 
