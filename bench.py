@@ -822,8 +822,7 @@ def main():
 
     # the same iterations handed over through host memory: counts and
     # background from host arrays, the image back to a host array (set_data
-    # drops the captured graphs, so the iterations' graph is captured again
-    # inside this region, as it would be for a caller doing the same)
+    # with the same parameters keeps the captured graphs)
     torch.cuda.synchronize()
     t_h = time.perf_counter()
     R.set_data(prob.y, prob.r, prob.beta, prob.rho, prob.sweeps)
@@ -832,7 +831,7 @@ def main():
     host_s = time.perf_counter() - t_h
     host_leg = {"value": args.steps / host_s, "unit": "iters/s", "seconds": host_s,
                 "note": "set_data from host arrays (y, r: %.1f MB), %d iterations, the image to a host array "
-                        "(%.1f MB), wall clock; the iteration graph is captured again after set_data"
+                        "(%.1f MB), wall clock; the iteration graph is kept over set_data"
                         % (8e-6 * prob.I, args.steps, 4e-6 * prob.J)}
     log("host-memory handover: %.1f iters/s (%.3f s for %d iterations)" % (host_leg["value"], host_s, args.steps))
 
