@@ -118,7 +118,8 @@ int sgtv_set_system(sgtv_ctx ctx, int64_t I, int32_t ny, int32_t nx, int32_t Q,
  * the ADMM penalty rho = lambda > 0 (Eqs. 4-6) and the number of surrogate
  * sweeps per image update (>= 1).  Resets the state: f = kappa * 1 with
  * kappa = sum(y) / sum(A^T 1) (the count-matched uniform start), d = c = 0,
- * k = 0.  Requires a system.
+ * k = 0.  Requires a system.  Device arrays may still be written by the null
+ * stream (or by blocking streams) when the call is made: it waits for them.
  */
 int sgtv_set_data(sgtv_ctx ctx, const float *y, const float *r, double beta, double rho,
                   int sweeps, int mem_kind);
@@ -337,8 +338,8 @@ int sgtv_backprojection_noalloc(sgtv_ctx ctx, float *x, int mem_kind);
  *     flight per wave, 2 two batches, 3 two batches plus the next column block
  *     read ahead into registers (0: automatic).  Variant 1 streams its lists
  *     with two-byte indices where rows_per_wave >= 64, block_cols <= 16380 is a
- *     multiple of 4 and at most 1024 * waves, and the matrix is dense enough for
- *     it; else it stores the indices in 24 bits (three bytes per entry instead
+ *     multiple of 4 and at most 1024 * waves, a slab has three column blocks, and
+ *     the padding of sparse lists stays within bounds; else it stores the indices in 24 bits (three bytes per entry instead
  *     of four) when 64 <= rows_per_wave <= 1024 and block_cols <= 16380, or
  *     1024 < rows_per_wave <= 2048 and block_cols <= 8188.
  * Limits: waves in [1, 16]; rows_per_wave in [1, 32767]; block_cols a
